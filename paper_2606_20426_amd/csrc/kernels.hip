@@ -52,28 +52,91 @@ __device__ __forceinline__ bool dir_ready(const EnvState* S) {
   return running(S) && S->stage == ST_CG && S->cg_done;
 }
 
-// CG iterations pending (the first product moves the pad from ST_ASM to ST_CG)
-__device__ __forceinline__ bool cg_running(const EnvState* S) {
-  return running(S) && (S->stage == ST_ASM || S->stage == ST_CG) && !S->cg_done;
+struct OpSum {
+  __device__ double operator()(double a, double b) const { return a + b; }
+};
+struct OpMax {
+  __device__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+struct OpMin {
+  __device__ double operator()(double a, double b) const { return fmin(a, b); }
+};
+
+// Pointers into global memory.  The descriptors hold plain pointers, through
+// which the compiler must use flat instructions: those count against LDS waits
+// too, so a load issued ahead of a reduction would be waited for inside it.
+// The hot kernels read the descriptor's pointers as global ones, once.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define TC_GLOBAL __attribute__((address_space(1)))
+#else
+#define TC_GLOBAL
+#endif
+template <class T> using gptr = TC_GLOBAL T*;
+template <class T> __device__ __forceinline__ gptr<T> glob(T* p) { return (gptr<T>)p; }
+template <class T> __device__ __forceinline__ gptr<T> glob_as(void* p) { return (gptr<T>)(T*)p; }
+template <class T> __device__ __forceinline__ gptr<const T> glob_as(const void* p) { return (gptr<const T>)(const T*)p; }
+
+// Lane exchange inside rows of 16 lanes by DPP (row_ror:N), in the VALU: a
+// butterfly through LDS (ds_bpermute) waits for the LDS at every level.
+template <int N> __device__ __forceinline__ float row_ror(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ double row_ror(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true));
+}
+// Sum over each row of 16 lanes, in every lane of the row (all lanes active).
+// Rotations by 8, 4, 2, 1 add the same pairs as a xor butterfly.
+template <typename R> __device__ __forceinline__ R row_sum16(R v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  return v + row_ror<1>(v);
 }
 
-struct OpSum { __device__ double operator()(double a, double b) const { return a + b; } };
-struct OpMax { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
-struct OpMin { __device__ double operator()(double a, double b) const { return fmin(a, b); } };
+// The two operands of a butterfly level across rows: lane l gets the values of
+// lanes l and l ^ ROWS * 16 (gfx950's row swaps), lower lane first.
+struct Pair { double lo, hi; };
+template <int ROWS> __device__ __forceinline__ Pair row_swap(double v) {
+  const unsigned a = __double2loint(v), b = __double2hiint(v);
+  if constexpr (ROWS == 2) {
+    const auto p = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return {__hiloint2double(q[0], p[0]), __hiloint2double(q[1], p[1])};
+  } else {
+    const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    return {__hiloint2double(q[0], p[0]), __hiloint2double(q[1], p[1])};
+  }
+}
 
-// Block-wide reduction, identical result in every thread.  Butterfly within
-// each wave (pairs add in both orders -> bitwise equal lanes), then every
-// thread folds the per-wave values in wave order.  Must be reached by all
-// threads of the block.
+// Butterfly reduction over the wave (distances 32 to 1), the same value in
+// every lane; all lanes active.
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  const Pair a = row_swap<2>(v);
+  v = op(a.lo, a.hi);
+  const Pair b = row_swap<1>(v);
+  v = op(b.lo, b.hi);
+  v = op(v, row_ror<8>(v));
+  v = op(v, row_ror<4>(v));
+  v = op(v, row_ror<2>(v));
+  return op(v, row_ror<1>(v));
+}
+
+// Block-wide reduction, identical result in every thread: within each wave,
+// then every thread folds the per-wave values in wave order.  Must be reached
+// by all threads of the block.
 template <class Op>
 __device__ double block_reduce(double v, Op op, double* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+  v = wave_reduce(v, op);
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[w] = v;
   __syncthreads();
+  if (nw == 4) return op(op(op(sh[0], sh[1]), sh[2]), sh[3]);   // the usual block
   double r = sh[0];
+#pragma unroll 1
   for (int k = 1; k < nw; ++k) r = op(r, sh[k]);
   return r;
 }
@@ -84,6 +147,37 @@ __device__ double reduce_partials(const double* p, int n, Op op, double init, do
   for (int i = threadIdx.x; i < n; i += blockDim.x) v = op(v, p[i]);
   return block_reduce(v, op, sh);
 }
+
+// Sum of a pad's n >= 1 partials, the same in every thread of every block.
+// Up to 512 each wave sums them itself, in the order of a block of four waves:
+// eight loads a lane, which the constructor issues and sum() waits for, and no
+// barrier; more are shared out over the block.
+struct PartialSum {
+  static constexpr int K = 8;
+  double t[K], v;
+  int n;
+  __device__ __forceinline__ PartialSum(gptr<const double> p, int n_) : v(0.0), n(n_) {
+    if (n > 64 * K)
+      for (int i = threadIdx.x; i < n; i += blockDim.x) v += p[i];
+#pragma unroll
+    for (int k = 0; k < K; ++k) t[k] = p[min((int)(threadIdx.x & 63) + 64 * k, n - 1)];
+  }
+  __device__ __forceinline__ double sum(double* sh) const {
+    if (n > 64 * K) return block_reduce(v, OpSum(), sh);
+    double s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s[k] = (int)(threadIdx.x & 63) + 64 * k < n ? t[k] : 0.0;
+      if ((int)(threadIdx.x & 63) + 64 * (k + 4) < n) s[k] += t[k + 4];
+    }
+    double r = wave_reduce(s[0], OpSum());
+    if (n <= 64) return r;
+    r += wave_reduce(s[1], OpSum());
+    if (n <= 128) return r;
+    const double a = wave_reduce(s[2], OpSum()), b = wave_reduce(s[3], OpSum());
+    return (r + a) + b;
+  }
+};
 
 template <typename R> __device__ __forceinline__ R rsq(R x);
 template <> __device__ __forceinline__ float rsq<float>(float x) { return 1.0f / sqrtf(x); }
@@ -1948,6 +2042,7 @@ __global__ void k_env_newton_begin(const EnvDesc* envs, int n) {
   // warm start from the previous Newton direction of this step (still in d)
   S->warm = envs[blockIdx.x].cg_warm && S->newton_iters > 0 && S->apply;
   S->cg_done = 0;
+  S->cg_stop[0] = S->cg_stop[1] = 0;
   S->cg_iters = 0;
   S->breakdown = 0;
   S->true_hess = S->true_hess && !S->no_true_hess;
@@ -1962,36 +2057,6 @@ __global__ void k_env_newton_begin(const EnvDesc* envs, int n) {
   S->ls_expand_n = 0;
   S->ls_contracting = 0;
   S->stage = ST_ASM;
-}
-
-// Common head of the CG product for one tile: reduce this pad's r.z
-// partials, decide whether its CG stops here (r.z <= tol^2 r0.z0, max_cg or a
-// breakdown) and publish the iteration's scalars (tile 0).  Every block of the
-// pad computes the same decision.  Returns false when the tile has no work;
-// else beta for p_new = z + beta p_old.
-__device__ __forceinline__ bool cg_go(const EnvDesc& E) {
-  EnvState* S = E.st;
-  // tile 0 of the pad may set cg_done while this block reads it: one thread
-  // reads, the block follows, so that all its waves take the same path
-  __shared__ int s_go;
-  if (threadIdx.x == 0) s_go = cg_running(S);
-  __syncthreads();
-  const bool go = s_go != 0;
-  __syncthreads();
-  return go;
-}
-
-// The stop decision on r.z (forcing term at the first iteration); tile 0
-// publishes the iteration's scalars.  False: this pad's CG has ended.
-__device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, int parity, double rz, double* beta,
-                                          int* it_out);
-
-__device__ __forceinline__ bool cg_head(const Tile tl, const EnvDesc& E, int parity, double* sh,
-                                        double* beta) {
-  if (!cg_go(E)) return false;
-  const double rz = reduce_partials(E.part_rz, E.n_vt, OpSum(), 0.0, sh);
-  int it;
-  return cg_decide(tl, E, parity, rz, beta, &it);
 }
 
 // Forcing term of a Newton iteration's solve, from its cold-start r0.z0:
@@ -2016,18 +2081,48 @@ __device__ __forceinline__ double cg_tol2_of(const EnvDesc& E, const EnvState* S
   return eta * eta;
 }
 
-__device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, int parity, double rz, double* beta,
-                                          int* it_out) {
-  EnvState* S = E.st;
-  const int it = S->it[parity ^ 1] + 1;
-  *it_out = it;
+// What the CG kernels read of a pad's state, all of it at once (a chain of
+// tests, each waiting for its own load, cost several memory latencies a
+// launch).  While a product runs, its tile 0 writes only what the other blocks
+// of that launch do not read: the slots of its own parity, and the stage
+// (ST_ASM and ST_CG both let them run).
+struct CgState {
+  bool go;                 // CG pending
+  bool stopped;            // ended in an earlier launch
+  int it, warm, breakdown;
+  double rz0, tol2, rzp;
+};
+
+// `slot`: the parity whose results are read (the product: the other one, the
+// update: its own).
+__device__ __forceinline__ CgState cg_state(gptr<const EnvState> S, int slot) {
+  const int phase = S->phase, status = S->status, stage = S->stage, stop = S->cg_stop[slot];
+  CgState c;
+  c.it = S->it[slot];
+  c.warm = S->warm;
+  c.breakdown = S->breakdown;
+  c.rz0 = S->rz0;
+  c.tol2 = S->cg_tol2;
+  c.rzp = S->rzp[slot];
+  const bool in = (phase == PH_RUN) & (status == TC_OK) & ((stage == ST_ASM) | (stage == ST_CG));
+  c.stopped = in & (stop != 0);
+  c.go = in & (stop == 0);
+  return c;
+}
+
+// The stop decision on r.z (forcing term at the first iteration), the same in
+// every block of the pad; tile 0 publishes the iteration's scalars.  False:
+// this pad's CG has ended.  Else beta for p_new = z + beta p_old.
+__device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, const CgState& c, int parity, double rz,
+                                          double* beta) {
+  const int it = c.it + 1;
   // iteration -1 of a warm start is the product with p = d_prev (z = 0,
   // beta 1); the solve's tolerance is set there, or at iteration 0 of a cold
   // start, from the cold start's r0.z0 (the partials of the assembly)
-  const bool first = it < 0 || (it == 0 && !S->warm);
-  const double rz0 = first ? rz : S->rz0;
-  const double tol2 = first ? cg_tol2_of(E, S, rz) : S->cg_tol2;
-  const bool done = it >= 0 && (it >= E.max_cg || !(rz > tol2 * rz0) || S->breakdown);
+  const bool first = it < 0 || (it == 0 && !c.warm);
+  const double rz0 = first ? rz : c.rz0;
+  const double tol2 = first ? cg_tol2_of(E, E.st, rz) : c.tol2;
+  const bool done = it >= 0 && (it >= E.max_cg || !(rz > tol2 * rz0) || c.breakdown);
   double gd = 0.0;
   if (it < 0 && tl.tile == 0) {
     // r0.d_prev from the assembly's partials (block-uniform branch)
@@ -2035,8 +2130,7 @@ __device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, int p
     gd = reduce_partials(E.part_dir, E.n_vt, OpSum(), 0.0, shd);
   }
   if (tl.tile == 0 && threadIdx.x == 0) {
-    // the other blocks of this launch read the stage: ST_ASM and ST_CG
-    // both let them run
+    gptr<EnvState> S = glob(E.st);
     S->stage = ST_CG;
     if (first) {
       S->cg_tol2 = tol2;
@@ -2044,6 +2138,7 @@ __device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, int p
     }
     if (done) {
       S->cg_done = 1;
+      S->cg_stop[parity] = 1;
       S->cg_iters = it;
     } else {
       S->it[parity] = it;
@@ -2051,7 +2146,7 @@ __device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, int p
     }
   }
   if (done) return false;
-  *beta = it < 0 ? 1.0 : it == 0 ? 0.0 : rz / S->rzp[parity ^ 1];
+  *beta = it < 0 ? 1.0 : it == 0 ? 0.0 : rz / c.rzp;
   return true;
 }
 
@@ -2092,136 +2187,260 @@ __device__ __forceinline__ void cg_spmv_rows_body(const Tile tl, const EnvDesc& 
 // The same product with LPR lanes per matrix row (lane l takes the stored
 // 3x3 blocks l, l + LPR, ... of its row, blocks of a row contiguous): every
 // lane issues its own independent neighbour gathers, and the row sum is a
-// shuffle reduction inside the lane group.  A row's padding slots (col -1)
-// come after its blocks, so a lane stops at its first one.  A tile is
-// blockDim.x / LPR lane groups x SPMV_ROWS_PER_GROUP rows.
+// reduction inside the lane group.  A row's padding slots (col -1) come after
+// its blocks, so a lane stops at its first one.  A tile is blockDim.x / LPR
+// lane groups x SPMV_ROWS_PER_GROUP rows.
+//
+// Rows that fit the lanes (W <= LPR) are loaded SPMV_AHEAD at a time: their
+// blocks, z and p_old need neither beta nor the stop decision, so a tile's
+// first rows are on their way while the block sums r.z.  What bounds a launch
+// over a few hundred tiles is this chain of loads (tile, descriptor, state and
+// columns, blocks), about 0.7 us each, and the reductions; over thousands of
+// tiles, the waves in flight: two rows ahead (76 VGPRs in float) ran the 1.2M
+// tet pad's step 3 % faster than four (110), and a 120k tet one 2.5 % slower.
+// With flat loads, the state tested field by field and reductions through
+// LDS, two steps of the 1.2M tet pad took 95.7 instead of 83.5 ms, of the 120k
+// tet one 34.3 instead of 27.5, and of a 1.9k tet one in FP64 20.0 instead of
+// 15.4, with the same bits.
+constexpr int SPMV_AHEAD = 2;
+
+template <typename R>
+struct SpmvSlot {
+  R a[9], z[3], p[3];
+};
+
+// One lane's part of the tile's matrix and vectors.
+template <typename R>
+struct SpmvTile {
+  gptr<const R> A;         // blocks of the tile's first row
+  gptr<const int32_t> col;
+  gptr<const R> z, pold;
+  gptr<R> pnew, q;
+  int V, W, row0;          // row0: first row of this lane's group
+};
+
 template <typename R, int LPR>
-__device__ __forceinline__ void cg_spmv_lanes_body(const Tile tl, const EnvDesc& E, int parity, R beta, double* sh) {
+__device__ __forceinline__ SpmvTile<R> spmv_tile(const Tile tl, const EnvDesc& E, int parity) {
+  SpmvTile<R> T;
+  const int first = tl.tile * (int)(blockDim.x / LPR) * SPMV_ROWS_PER_GROUP;
+  T.V = E.V;
+  T.W = E.W;
+  T.row0 = first + threadIdx.x / LPR;
+  T.A = glob_as<R>((const void*)E.A) + (size_t)first * T.W * 9;
+  T.col = glob(E.col) + (size_t)first * T.W;
+  T.z = glob_as<R>((const void*)E.z);
+  T.pold = glob_as<R>((const void*)(parity ? E.p0 : E.p1));
+  T.pnew = glob_as<R>(parity ? E.p1 : E.p0);
+  T.q = glob_as<R>(E.q);
+  return T;
+}
+
+// Columns of the lane's slots in rows k0 .. of its group; -1: no block.
+template <typename R, int LPR>
+__device__ __forceinline__ void spmv_cols(const SpmvTile<R>& T, int k0, int (&j)[SPMV_AHEAD]) {
   const int lane = threadIdx.x & (LPR - 1);
   const int groups = blockDim.x / LPR;
-  const R* z = (const R*)E.z;
-  const R* pold = (const R*)(parity ? E.p0 : E.p1);
-  R* pnew = (R*)(parity ? E.p1 : E.p0);
-  R* q = (R*)E.q;
-  double pq = 0.0;
-  const int row0 = tl.tile * groups * SPMV_ROWS_PER_GROUP + threadIdx.x / LPR;
-#pragma unroll 2
-  for (int k = 0; k < SPMV_ROWS_PER_GROUP; ++k) {
-    const int i = row0 + k * groups;
-    R y0 = 0, y1 = 0, y2 = 0, pd0 = 0, pd1 = 0, pd2 = 0;
-    if (E.W <= LPR) {             // one slot per lane (the common case)
-      if (i < E.V && lane < E.W) {
-        const size_t item = (size_t)i * E.W + lane;
-        const int j = E.col[item];
-        if (j >= 0) {
-          pd0 = z[3 * j] + beta * pold[3 * j];
-          pd1 = z[3 * j + 1] + beta * pold[3 * j + 1];
-          pd2 = z[3 * j + 2] + beta * pold[3 * j + 2];
-          const R* As = (const R*)E.A + item * 9;
-          y0 = As[0] * pd0 + As[1] * pd1 + As[2] * pd2;
-          y1 = As[3] * pd0 + As[4] * pd1 + As[5] * pd2;
-          y2 = As[6] * pd0 + As[7] * pd1 + As[8] * pd2;
-        }
-      }
-    } else if (i < E.V) {
-      for (int sl = lane; sl < E.W; sl += LPR) {
-        const size_t item = (size_t)i * E.W + sl;
-        const int j = E.col[item];
-        if (j < 0) break;
-        const R pj0 = z[3 * j] + beta * pold[3 * j];
-        const R pj1 = z[3 * j + 1] + beta * pold[3 * j + 1];
-        const R pj2 = z[3 * j + 2] + beta * pold[3 * j + 2];
-        if (sl == 0) { pd0 = pj0; pd1 = pj1; pd2 = pj2; }
-        const R* As = (const R*)E.A + item * 9;
-        y0 += As[0] * pj0 + As[1] * pj1 + As[2] * pj2;
-        y1 += As[3] * pj0 + As[4] * pj1 + As[5] * pj2;
-        y2 += As[6] * pj0 + As[7] * pj1 + As[8] * pj2;
-      }
-    }
+  const int last = T.V - 1 - (T.row0 - (int)(threadIdx.x / LPR));   // the pad's last row within the tile
 #pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) {
-      y0 += __shfl_xor(y0, o, LPR);
-      y1 += __shfl_xor(y1, o, LPR);
-      y2 += __shfl_xor(y2, o, LPR);
-    }
-    if (lane == 0 && i < E.V) {   // slot 0 is the diagonal: pd = p_new of row i
-      pnew[3 * i] = pd0; pnew[3 * i + 1] = pd1; pnew[3 * i + 2] = pd2;
-      q[3 * i] = y0; q[3 * i + 1] = y1; q[3 * i + 2] = y2;
-      pq += (double)pd0 * y0 + (double)pd1 * y1 + (double)pd2 * y2;
+  for (int u = 0; u < SPMV_AHEAD; ++u)
+    j[u] = T.col[(unsigned)(min((int)(threadIdx.x / LPR) + (k0 + u) * groups, last) * T.W + min(lane, T.W - 1))];
+#pragma unroll
+  for (int u = 0; u < SPMV_AHEAD; ++u)
+    if (T.row0 + (k0 + u) * groups >= T.V || lane >= T.W) j[u] = -1;
+}
+
+// Their blocks and vectors, without branches (a skipped load would make every
+// later wait one for all loads): a lane without a block reads the tile's first
+// row and its result is dropped.
+template <typename R, int LPR>
+__device__ __forceinline__ void spmv_load(const SpmvTile<R>& T, int k0, const int (&j)[SPMV_AHEAD],
+                                          SpmvSlot<R> (&s)[SPMV_AHEAD]) {
+  const int lane = threadIdx.x & (LPR - 1);
+  const int groups = blockDim.x / LPR;
+#pragma unroll
+  for (int u = 0; u < SPMV_AHEAD; ++u) {
+    const bool ok = j[u] >= 0;
+    gptr<const R> As = T.A + (ok ? 9u * (unsigned)((threadIdx.x / LPR + (k0 + u) * groups) * T.W + lane) : 0u);
+    gptr<const R> zj = T.z + 3 * (size_t)(ok ? j[u] : 0);
+    gptr<const R> pj = T.pold + 3 * (size_t)(ok ? j[u] : 0);
+#pragma unroll
+    for (int c = 0; c < 9; ++c) s[u].a[c] = As[c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      s[u].z[c] = zj[c];
+      s[u].p[c] = pj[c];
     }
   }
-  pq = block_reduce(pq, OpSum(), sh);
-  if (threadIdx.x == 0) E.part_pq[tl.tile] = pq;
 }
 
-// The product of one SpMV tile given beta (p_new = z + beta p_old).
 template <typename R, int LPR>
-__device__ __forceinline__ void cg_spmv_body(const Tile tl, const EnvDesc& E, int parity, R beta, double* sh) {
-  if constexpr (LPR == 0) cg_spmv_rows_body<R>(tl, E, parity, beta, sh);
-  else cg_spmv_lanes_body<R, LPR>(tl, E, parity, beta, sh);
+__device__ __forceinline__ double cg_spmv_lanes_body(const SpmvTile<R>& T, R beta, int (&j)[SPMV_AHEAD],
+                                                     SpmvSlot<R> (&s)[SPMV_AHEAD]) {
+  const int lane = threadIdx.x & (LPR - 1);
+  const int groups = blockDim.x / LPR;
+  double pq = 0.0;
+  auto finish = [&](int i, R y0, R y1, R y2, R pd0, R pd1, R pd2) {
+    if constexpr (LPR == 32) {
+      y0 += __shfl_xor(y0, 16, 32);
+      y1 += __shfl_xor(y1, 16, 32);
+      y2 += __shfl_xor(y2, 16, 32);
+    }
+    y0 = row_sum16(y0);
+    y1 = row_sum16(y1);
+    y2 = row_sum16(y2);
+    if (lane == 0 && i < T.V) {   // slot 0 is the diagonal: pd = p_new of row i
+      gptr<R> pn = T.pnew + 3 * (size_t)i;
+      gptr<R> qn = T.q + 3 * (size_t)i;
+      pn[0] = pd0; pn[1] = pd1; pn[2] = pd2;
+      qn[0] = y0; qn[1] = y1; qn[2] = y2;
+      pq += (double)pd0 * y0 + (double)pd1 * y1 + (double)pd2 * y2;
+    }
+  };
+  if (T.W <= LPR) {               // one slot per lane (the common case)
+#pragma unroll
+    for (int k0 = 0; k0 < SPMV_ROWS_PER_GROUP; k0 += SPMV_AHEAD) {
+      if (k0 > 0) {
+        spmv_cols<R, LPR>(T, k0, j);
+        spmv_load<R, LPR>(T, k0, j, s);
+      }
+#pragma unroll
+      for (int u = 0; u < SPMV_AHEAD; ++u) {
+        const R* As = s[u].a;
+        const bool ok = j[u] >= 0;
+        const R pd0 = s[u].z[0] + beta * s[u].p[0];
+        const R pd1 = s[u].z[1] + beta * s[u].p[1];
+        const R pd2 = s[u].z[2] + beta * s[u].p[2];
+        finish(T.row0 + (k0 + u) * groups, ok ? As[0] * pd0 + As[1] * pd1 + As[2] * pd2 : R(0),
+               ok ? As[3] * pd0 + As[4] * pd1 + As[5] * pd2 : R(0),
+               ok ? As[6] * pd0 + As[7] * pd1 + As[8] * pd2 : R(0), pd0, pd1, pd2);
+      }
+    }
+  } else {
+#pragma unroll 2
+    for (int k = 0; k < SPMV_ROWS_PER_GROUP; ++k) {
+      const int i = T.row0 + k * groups;
+      R y0 = 0, y1 = 0, y2 = 0, pd0 = 0, pd1 = 0, pd2 = 0;
+      if (i < T.V) {
+        for (int sl = lane; sl < T.W; sl += LPR) {
+          const unsigned item = (threadIdx.x / LPR + k * groups) * T.W + sl;
+          const int j = T.col[item];
+          if (j < 0) break;
+          gptr<const R> zj = T.z + 3 * (size_t)j;
+          gptr<const R> pj = T.pold + 3 * (size_t)j;
+          gptr<const R> As = T.A + 9u * item;
+          const R pj0 = zj[0] + beta * pj[0];
+          const R pj1 = zj[1] + beta * pj[1];
+          const R pj2 = zj[2] + beta * pj[2];
+          if (sl == 0) { pd0 = pj0; pd1 = pj1; pd2 = pj2; }
+          y0 += As[0] * pj0 + As[1] * pj1 + As[2] * pj2;
+          y1 += As[3] * pj0 + As[4] * pj1 + As[5] * pj2;
+          y2 += As[6] * pj0 + As[7] * pj1 + As[8] * pj2;
+        }
+      }
+      finish(i, y0, y1, y2, pd0, pd1, pd2);
+    }
+  }
+  return pq;
 }
 
+// The product of one SpMV tile (p_new = z + beta p_old).  Everything of the
+// descriptor is read before the state is tested: the loads go out together.
 template <typename R, int LPR>
 __device__ __forceinline__ void cg_spmv_tile(const Tile tl, const EnvDesc* envs, int parity, double* sh) {
   const EnvDesc& E = envs[tl.env];
+  gptr<EnvState> S = glob(E.st);
+  gptr<const double> part_rz = glob((const double*)E.part_rz);
+  gptr<double> part_pq = glob(E.part_pq) + tl.tile;
+  const int n_vt = E.n_vt;
+  const SpmvTile<R> T = spmv_tile<R, LPR == 0 ? 1 : LPR>(tl, E, parity);
+  asm volatile("" ::"s"(part_rz), "s"(part_pq), "s"(n_vt), "s"(T.A), "s"(T.col), "s"(T.z), "s"(T.pold), "s"(T.pnew),
+               "s"(T.q), "s"(T.V), "s"(T.W));
+  // columns and r.z partials go out with the state: a tile of a pad that has
+  // stopped reads them in vain (a tenth of its bytes), the others save the
+  // state's latency
+  const CgState c = cg_state((gptr<const EnvState>)S, parity ^ 1);
+  int j[SPMV_AHEAD];
+  if constexpr (LPR > 0) spmv_cols<R, LPR>(T, 0, j);
+  const PartialSum rz(part_rz, n_vt);
+  if (!c.go) {
+    // later launches read the stop from either slot
+    if (c.stopped && tl.tile == 0 && threadIdx.x == 0) S->cg_stop[parity] = 1;
+    return;
+  }
   double beta;
-  if (!cg_head(tl, E, parity, sh, &beta)) return;
-  cg_spmv_body<R, LPR>(tl, E, parity, (R)beta, sh);
+  if constexpr (LPR == 0) {
+    if (!cg_decide(tl, E, c, parity, rz.sum(sh), &beta)) return;
+    cg_spmv_rows_body<R>(tl, E, parity, (R)beta, sh);
+  } else {
+    SpmvSlot<R> s[SPMV_AHEAD];
+    if (T.W <= LPR) spmv_load<R, LPR>(T, 0, j, s);
+    if (!cg_decide(tl, E, c, parity, rz.sum(sh), &beta)) return;
+    const double pq = block_reduce(cg_spmv_lanes_body<R, LPR>(T, (R)beta, j, s), OpSum(), sh);
+    if (threadIdx.x == 0) *part_pq = pq;
+  }
 }
 
-// alpha = r.z / p.Ap; d += alpha p; r -= alpha Ap (float64); z = P^-1 r;
-// partial r.z for the next iteration.
-// alpha = r.z / p.Ap from the product's partials (a non-positive p.Ap is a
-// breakdown: alpha = 0 and the tile-0 block flags it).
-__device__ __forceinline__ double cg_alpha(const Tile tl, const EnvDesc& E, int parity, double* sh) {
-  EnvState* S = E.st;
-  const double pq = reduce_partials(E.part_pq, E.n_spt, OpSum(), 0.0, sh);
-  const double rz = S->rzp[parity];
-  double alpha = rz / pq;
+// alpha = r.z / p.Ap (a non-positive p.Ap is a breakdown: alpha = 0 and the
+// tile-0 block flags it); d += alpha p; r -= alpha Ap (float64); z = P^-1 r;
+// partial r.z for the next iteration.  The row's vectors do not need alpha:
+// they are loaded while the block sums p.Ap.
+template <typename R>
+__device__ __forceinline__ void cg_update_tile(const Tile tl, const EnvDesc* envs, int parity, double* sh) {
+  const EnvDesc& E = envs[tl.env];
+  gptr<EnvState> S = glob(E.st);
+  const int V = E.V, n_spt = E.n_spt;
+  const int i = tl.tile * blockDim.x + threadIdx.x;
+  const bool in = i < V;
+  const size_t row = in ? i : 0;
+  gptr<const double> part_pq = glob((const double*)E.part_pq);
+  gptr<double> part_rz = glob(E.part_rz) + tl.tile;
+  gptr<R> d = glob_as<R>(E.d) + 3 * row;
+  gptr<R> z = glob_as<R>(E.z) + 3 * row;
+  gptr<double> r = glob(E.r) + 3 * row;
+  gptr<const R> pp = glob_as<R>((const void*)(parity ? E.p1 : E.p0)) + 3 * row;
+  gptr<const R> qq = glob_as<R>((const void*)E.q) + 3 * row;
+  gptr<const R> Pp = glob_as<R>((const void*)E.Pinv) + 6 * row;
+  asm volatile("" ::"s"(part_pq), "s"(n_spt));
+  const CgState c = cg_state((gptr<const EnvState>)S, parity);
+  const PartialSum pqs(part_pq, n_spt);
+  if (!c.go) return;
+  R p[3], q[3], dv[3], Pi[6];
+  double rr[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p[k] = pp[k];
+    q[k] = qq[k];
+    dv[k] = d[k];
+    rr[k] = r[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) Pi[k] = Pp[k];
+  const double pq = pqs.sum(sh);
+  double alpha = c.rzp / pq;
   if (!(pq > 0.0) || !isfinite(alpha)) {
     alpha = 0.0;
     // (a warm start along a direction of non-positive curvature is only
     // skipped: the cold start follows)
-    if (tl.tile == 0 && threadIdx.x == 0 && S->it[parity] >= 0) S->breakdown = 1;
+    if (tl.tile == 0 && threadIdx.x == 0 && c.it >= 0) S->breakdown = 1;
   }
-  return alpha;
-}
-
-template <typename R>
-__device__ __forceinline__ void cg_update_body(const Tile tl, const EnvDesc& E, int parity, double alpha,
-                                               double* sh) {
-  const int i = tl.tile * blockDim.x + threadIdx.x;
   double rzn = 0.0;
-  if (i < E.V) {
-    const R* p = (const R*)(parity ? E.p1 : E.p0);
-    const R* q = (const R*)E.q;
-    R* d = (R*)E.d;
-    R* z = (R*)E.z;
-    const R* Pi = (const R*)E.Pinv + 6 * i;
+  if (in) {
     const R a = (R)alpha;
-    double rr[3];
-    for (int c = 0; c < 3; ++c) {
-      d[3 * i + c] += a * p[3 * i + c];
-      rr[c] = E.r[3 * i + c] - alpha * (double)q[3 * i + c];
-      E.r[3 * i + c] = rr[c];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      d[k] = dv[k] + a * p[k];
+      rr[k] -= alpha * (double)q[k];
+      r[k] = rr[k];
     }
     const R r0 = (R)rr[0], r1 = (R)rr[1], r2 = (R)rr[2];
     const R z0 = Pi[0] * r0 + Pi[1] * r1 + Pi[2] * r2;
     const R z1 = Pi[1] * r0 + Pi[3] * r1 + Pi[4] * r2;
     const R z2 = Pi[2] * r0 + Pi[4] * r1 + Pi[5] * r2;
-    z[3 * i] = z0; z[3 * i + 1] = z1; z[3 * i + 2] = z2;
+    z[0] = z0; z[1] = z1; z[2] = z2;
     rzn = rr[0] * (double)z0 + rr[1] * (double)z1 + rr[2] * (double)z2;
   }
   rzn = block_reduce(rzn, OpSum(), sh);
-  if (threadIdx.x == 0) E.part_rz[tl.tile] = rzn;
-}
-
-template <typename R>
-__device__ __forceinline__ void cg_update_tile(const Tile tl, const EnvDesc* envs, int parity, double* sh) {
-  const EnvDesc& E = envs[tl.env];
-  EnvState* S = E.st;
-  if (!cg_running(S)) return;
-  cg_update_body<R>(tl, E, parity, cg_alpha(tl, E, parity, sh), sh);
+  if (threadIdx.x == 0) *part_rz = rzn;
 }
 
 // Optional self-timing of a launch on the GPU wall clock: every block stores

@@ -157,6 +157,7 @@ struct EnvState {
   double rzp[2];
   double rz0;
   int32_t it[2];
+  int32_t cg_stop[2];      // CG ended, as the product of each parity saw it
   int32_t cg_done;
   int32_t warm;            // this iteration's CG starts from gamma d_prev (iteration -1)
   int32_t cg_iters;
