@@ -15,6 +15,11 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
+
+#if defined(__HIP_DEVICE_COMPILE__)
+#define TC_GLOBAL __attribute__((address_space(1)))
+#endif
 
 #include "../../include/tacauchy.h"
 #include "tc_device.h"
@@ -34,22 +39,34 @@ __device__ __forceinline__ int xcd_tile(int ntiles) {
   return t < ntiles ? t : -1;
 }
 
+// Tests of a pad's state.  The fields are read together and combined without
+// branches: tested one after another, each waits a memory latency of its own.
 __device__ __forceinline__ bool running(const EnvState* S) {
-  return S->phase == PH_RUN && S->status == TC_OK;
+  const int phase = S->phase, status = S->status;
+  return (phase == PH_RUN) & (status == TC_OK);
 }
 
 __device__ __forceinline__ bool initialising(const EnvState* S) {
-  return S->phase == PH_INIT && S->status == TC_OK;
+  const int phase = S->phase, status = S->status;
+  return (phase == PH_INIT) & (status == TC_OK);
 }
 
 __device__ __forceinline__ bool at_stage(const EnvState* S, int stage) {
-  return running(S) && S->stage == stage;
+  const int now = S->stage;
+  return running(S) & (now == stage);
+}
+
+// the line search of this Newton iteration goes on
+__device__ __forceinline__ bool searching(const EnvState* S) {
+  const int done = S->ls_done;
+  return at_stage(S, ST_LS) & (done == 0);
 }
 
 // the CG of this Newton iteration has ended: direction, filter and step
 // bound pending
 __device__ __forceinline__ bool dir_ready(const EnvState* S) {
-  return running(S) && S->stage == ST_CG && S->cg_done;
+  const int done = S->cg_done;
+  return at_stage(S, ST_CG) & (done != 0);
 }
 
 struct OpSum {
@@ -62,19 +79,8 @@ struct OpMin {
   __device__ double operator()(double a, double b) const { return fmin(a, b); }
 };
 
-// Pointers into global memory.  The descriptors hold plain pointers, through
-// which the compiler must use flat instructions: those count against LDS waits
-// too, so a load issued ahead of a reduction would be waited for inside it.
-// The hot kernels read the descriptor's pointers as global ones, once.
-#if defined(__HIP_DEVICE_COMPILE__)
-#define TC_GLOBAL __attribute__((address_space(1)))
-#else
-#define TC_GLOBAL
-#endif
+// pointer into global memory (see TC_GLOBAL)
 template <class T> using gptr = TC_GLOBAL T*;
-template <class T> __device__ __forceinline__ gptr<T> glob(T* p) { return (gptr<T>)p; }
-template <class T> __device__ __forceinline__ gptr<T> glob_as(void* p) { return (gptr<T>)(T*)p; }
-template <class T> __device__ __forceinline__ gptr<const T> glob_as(const void* p) { return (gptr<const T>)(const T*)p; }
 
 // Lane exchange inside rows of 16 lanes by DPP (row_ror:N), in the VALU: a
 // butterfly through LDS (ds_bpermute) waits for the LDS at every level.
@@ -1466,7 +1472,7 @@ __global__ void k_pairs(const Tile* tiles, int ntiles, const EnvDesc* envs, int 
   const int j = tl.tile * blockDim.x + threadIdx.x;
   if (mode >= 2) {
     // block reductions: every thread of the block takes part
-    if (mode == 2 ? (!at_stage(S, ST_LS) || S->ls_done) : mode == 4 ? !initialising(S) : !dir_ready(S)) return;
+    if (mode == 2 ? !searching(S) : mode == 4 ? !initialising(S) : !dir_ready(S)) return;
     const bool in = j < E.S + E.Se;
     if (mode == 3) {
       double a = INFINITY;
@@ -1839,12 +1845,23 @@ __global__ void k_barrier(const Tile* tiles, int ntiles, const EnvDesc* envs) {
 // Diagonal block rows (slot 0): sum of element blocks, inertia, barrier,
 // Dirichlet masking, gradient, preconditioner, and CG initialisation
 // (d = 0, r = -g, z = P^-1 r, partial r.z and g.g).  A tile is blockDim.x
-// rows; groups of ASM_LPR lanes take one row at a time, each lane summing
-// every ASM_LPR-th record of the row's contiguous run of diagonal-stream
-// records (so a wavefront reads a few long runs instead of 64 scattered
-// records), then a shuffle reduction gives the row's sums to its lane 0,
-// which finishes the row.
+// rows; groups of ASM_LPR lanes sum one row at a time, each lane taking every
+// ASM_LPR-th record of the row's contiguous run of diagonal-stream records (so
+// a wavefront reads a few long runs instead of 64 scattered records); lane k
+// keeps the sums of the group's row k, and every lane finishes one row.
 constexpr int ASM_LPR = 8;
+
+// Lane 0 of each 8 gets the sum of the 8 in the order of a xor butterfly (4, 2,
+// 1) by DPP; the other lanes' results are partial.
+template <int CTRL> __device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double sum8_lane0(double v) {
+  v += dpp<0x104>(v);           // row_shl:4
+  v += dpp<0xEE>(v);            // quad_perm [2, 3, 2, 3]
+  return v + dpp<0x55>(v);      // quad_perm [1, 1, 1, 1]
+}
 
 template <typename R>
 __device__ __forceinline__ void asm_diag_row(const EnvDesc& E, int i, double D[3][3], double gs[3], double& rz,
@@ -1940,25 +1957,74 @@ __global__ void k_asm_diag(const Tile* tiles, int ntiles, const EnvDesc* envs) {
   const int row0 = tl.tile * blockDim.x + threadIdx.x / ASM_LPR;
   const R* Kd = (const R*)E.Ke;
   const bool warm = E.cg_warm && E.st->warm != 0;
-  double rz = 0.0, gg = 0.0;
-  for (int k = 0; k < ASM_LPR; ++k) {
-    const int i = row0 + k * groups;
+  // row k of the group: summed by its lanes, kept by lane k.  The ranges of
+  // the group's rows are read at once, and where no row of the wave has more
+  // than 3 records a lane (24 tets, the inside of a grid) without branches, so
+  // that the records of several rows are on their way together.  Row by row,
+  // each waiting for its range and then for each record, with one lane in 8
+  // finishing the rows, a launch took 22 us at least (1.9k tets, FP64) and
+  // 72 us on the 60-pad batch; now 14 and 45.
+  const int row = row0 + lane * groups;
+  const int c_beg = row < E.V ? E.dptr[row] : 0;
+  const int c_end = row < E.V ? E.dptr[row + 1] : 0;
+  const bool few = !__any(c_end - c_beg > 3 * ASM_LPR);
+  double mine[9];
+  auto take = [&](auto kc, auto few_c) {
+    constexpr int k = decltype(kc)::value;
     double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // xx xy xz yy yz zz, gradient
-    if (i < E.V)
-      for (int c = E.dptr[i] + lane; c < E.dptr[i + 1]; c += ASM_LPR) {
+    const int c0 = __shfl(c_beg, k, ASM_LPR), c1 = __shfl(c_end, k, ASM_LPR);
+    if constexpr (decltype(few_c)::value) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int c = c0 + lane + u * ASM_LPR;
+        const R* p = Kd + (size_t)KC * min(c, max(c1 - 1, 0));
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+          const double t = (double)p[q];
+          v[q] += c < c1 ? t : 0.0;
+        }
+      }
+    } else {
+      for (int c = c0 + lane; c < c1; c += ASM_LPR) {
         const R* p = Kd + (size_t)KC * c;
 #pragma unroll
         for (int q = 0; q < 9; ++q) v[q] += (double)p[q];
       }
-#pragma unroll
-    for (int o = ASM_LPR / 2; o > 0; o >>= 1)
-#pragma unroll
-      for (int q = 0; q < 9; ++q) v[q] += __shfl_xor(v[q], o, ASM_LPR);
-    if (lane == 0 && i < E.V) {
-      double D[3][3] = {{v[0], v[1], v[2]}, {0, v[3], v[4]}, {0, 0, v[5]}};
-      double gs[3] = {v[6], v[7], v[8]};
-      asm_diag_row<R>(E, i, D, gs, rz, gg, warm);
     }
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      const double t = sum8_lane0(v[q]);
+      if constexpr (k == 0) {
+        mine[q] = t;
+      } else {
+        const double u = dpp<0x110 + k>(t);   // row_shr:k, every lane taking part
+        mine[q] = lane == k ? u : mine[q];
+      }
+    }
+  };
+  auto take_all = [&](auto few_c) {
+    take(std::integral_constant<int, 0>(), few_c); take(std::integral_constant<int, 1>(), few_c);
+    take(std::integral_constant<int, 2>(), few_c); take(std::integral_constant<int, 3>(), few_c);
+    take(std::integral_constant<int, 4>(), few_c); take(std::integral_constant<int, 5>(), few_c);
+    take(std::integral_constant<int, 6>(), few_c); take(std::integral_constant<int, 7>(), few_c);
+  };
+  if (few) take_all(std::true_type());
+  else take_all(std::false_type());
+  double rz = 0.0, gg = 0.0;
+  if (row < E.V) {
+    double D[3][3] = {{mine[0], mine[1], mine[2]}, {0, mine[3], mine[4]}, {0, 0, mine[5]}};
+    double gs[3] = {mine[6], mine[7], mine[8]};
+    asm_diag_row<R>(E, row, D, gs, rz, gg, warm);
+  }
+  // the group's rows in order, in its lane 0
+  {
+    double r = 0.0, g = 0.0;
+    for (int k = 0; k < ASM_LPR; ++k) {
+      r += __shfl(rz, k, ASM_LPR);
+      g += __shfl(gg, k, ASM_LPR);
+    }
+    rz = lane == 0 ? r : 0.0;
+    gg = lane == 0 ? g : 0.0;
   }
   rz = block_reduce(rz, OpSum(), sh);
   gg = block_reduce(gg, OpSum(), sh);
@@ -2130,7 +2196,7 @@ __device__ __forceinline__ bool cg_decide(const Tile tl, const EnvDesc& E, const
     gd = reduce_partials(E.part_dir, E.n_vt, OpSum(), 0.0, shd);
   }
   if (tl.tile == 0 && threadIdx.x == 0) {
-    gptr<EnvState> S = glob(E.st);
+    gptr<EnvState> S = E.st;
     S->stage = ST_CG;
     if (first) {
       S->cg_tol2 = tol2;
@@ -2226,12 +2292,12 @@ __device__ __forceinline__ SpmvTile<R> spmv_tile(const Tile tl, const EnvDesc& E
   T.V = E.V;
   T.W = E.W;
   T.row0 = first + threadIdx.x / LPR;
-  T.A = glob_as<R>((const void*)E.A) + (size_t)first * T.W * 9;
-  T.col = glob(E.col) + (size_t)first * T.W;
-  T.z = glob_as<R>((const void*)E.z);
-  T.pold = glob_as<R>((const void*)(parity ? E.p0 : E.p1));
-  T.pnew = glob_as<R>(parity ? E.p1 : E.p0);
-  T.q = glob_as<R>(E.q);
+  T.A = (gptr<const R>)E.A + (size_t)first * T.W * 9;
+  T.col = E.col + (size_t)first * T.W;
+  T.z = (gptr<const R>)E.z;
+  T.pold = (gptr<const R>)(parity ? E.p0 : E.p1);
+  T.pnew = (gptr<R>)(parity ? E.p1 : E.p0);
+  T.q = (gptr<R>)E.q;
   return T;
 }
 
@@ -2348,9 +2414,9 @@ __device__ __forceinline__ double cg_spmv_lanes_body(const SpmvTile<R>& T, R bet
 template <typename R, int LPR>
 __device__ __forceinline__ void cg_spmv_tile(const Tile tl, const EnvDesc* envs, int parity, double* sh) {
   const EnvDesc& E = envs[tl.env];
-  gptr<EnvState> S = glob(E.st);
-  gptr<const double> part_rz = glob((const double*)E.part_rz);
-  gptr<double> part_pq = glob(E.part_pq) + tl.tile;
+  gptr<EnvState> S = E.st;
+  gptr<const double> part_rz = E.part_rz;
+  gptr<double> part_pq = E.part_pq + tl.tile;
   const int n_vt = E.n_vt;
   const SpmvTile<R> T = spmv_tile<R, LPR == 0 ? 1 : LPR>(tl, E, parity);
   asm volatile("" ::"s"(part_rz), "s"(part_pq), "s"(n_vt), "s"(T.A), "s"(T.col), "s"(T.z), "s"(T.pold), "s"(T.pnew),
@@ -2387,19 +2453,19 @@ __device__ __forceinline__ void cg_spmv_tile(const Tile tl, const EnvDesc* envs,
 template <typename R>
 __device__ __forceinline__ void cg_update_tile(const Tile tl, const EnvDesc* envs, int parity, double* sh) {
   const EnvDesc& E = envs[tl.env];
-  gptr<EnvState> S = glob(E.st);
+  gptr<EnvState> S = E.st;
   const int V = E.V, n_spt = E.n_spt;
   const int i = tl.tile * blockDim.x + threadIdx.x;
   const bool in = i < V;
   const size_t row = in ? i : 0;
-  gptr<const double> part_pq = glob((const double*)E.part_pq);
-  gptr<double> part_rz = glob(E.part_rz) + tl.tile;
-  gptr<R> d = glob_as<R>(E.d) + 3 * row;
-  gptr<R> z = glob_as<R>(E.z) + 3 * row;
-  gptr<double> r = glob(E.r) + 3 * row;
-  gptr<const R> pp = glob_as<R>((const void*)(parity ? E.p1 : E.p0)) + 3 * row;
-  gptr<const R> qq = glob_as<R>((const void*)E.q) + 3 * row;
-  gptr<const R> Pp = glob_as<R>((const void*)E.Pinv) + 6 * row;
+  gptr<const double> part_pq = E.part_pq;
+  gptr<double> part_rz = E.part_rz + tl.tile;
+  gptr<R> d = (gptr<R>)E.d + 3 * row;
+  gptr<R> z = (gptr<R>)E.z + 3 * row;
+  gptr<double> r = E.r + 3 * row;
+  gptr<const R> pp = (gptr<const R>)(parity ? E.p1 : E.p0) + 3 * row;
+  gptr<const R> qq = (gptr<const R>)E.q + 3 * row;
+  gptr<const R> Pp = (gptr<const R>)E.Pinv + 6 * row;
   asm volatile("" ::"s"(part_pq), "s"(n_spt));
   const CgState c = cg_state((gptr<const EnvState>)S, parity);
   const PartialSum pqs(part_pq, n_spt);
@@ -2664,7 +2730,7 @@ __global__ void k_energy(const Tile* tiles, int ntiles, const EnvDesc* envs, int
   const EnvDesc& E = envs[tl.env];
   const EnvState* S = E.st;
   const EnvPose* P = E.pose;
-  if (mode == 0 ? !initialising(S) : (!at_stage(S, ST_LS) || S->ls_done)) return;
+  if (mode == 0 ? !initialising(S) : !searching(S)) return;
   const double al = mode == 0 ? 0.0 : S->ls_alpha;
   const R* d = (const R*)E.d;
   double acc = 0.0;
@@ -2763,7 +2829,7 @@ __global__ void k_env_ls(const EnvDesc* envs, int n, int mode) {
   if (blockIdx.x >= n) return;
   const EnvDesc& E = envs[blockIdx.x];
   EnvState* S = E.st;
-  if (mode == 0 ? !initialising(S) : (!at_stage(S, ST_LS) || S->ls_done)) return;
+  if (mode == 0 ? !initialising(S) : !searching(S)) return;
   double el = 0, in = 0, ba = 0;
   for (int k = threadIdx.x; k < E.n_te; k += blockDim.x) el += E.part_e[k];
   for (int k = threadIdx.x; k < E.n_vt; k += blockDim.x) in += E.part_e[E.n_te + k];
@@ -2883,7 +2949,8 @@ __global__ void k_env_update(const EnvDesc* envs, int n) {
 // ------------------------------------------------------ extraction (a8-a10)
 
 __device__ __forceinline__ bool extract_ok(const EnvState* S) {
-  return S->phase == PH_FINISH && S->status == TC_OK;
+  const int phase = S->phase, status = S->status;
+  return (phase == PH_FINISH) & (status == TC_OK);
 }
 
 // Eq. 4 per tet: sigma = (mu / J) F F^T + lam (J - alpha) I, Voigt order

@@ -5,6 +5,16 @@
 
 #include <cstdint>
 
+// The descriptor's pointers as the kernels see them: into global memory.  Read
+// as plain pointers they would be generic ones, through which the compiler
+// must use flat instructions; those count against LDS waits too and keep their
+// addresses in vector registers.  Host code (which the device pass of its
+// files parses as well) sees plain pointers: only kernels.hip, for the device,
+// sets the address space.  The layout is the same.
+#ifndef TC_GLOBAL
+#define TC_GLOBAL
+#endif
+
 namespace tc {
 
 constexpr int MAX_IND = 5;
@@ -63,18 +73,18 @@ struct DevMesh {
   int32_t n_tri, n_node;
   int32_t convex;          // 1: one component, no concave edge (the distance outside is convex)
   int32_t n_vert;
-  const double* tv;        // [n_tri][9] corners a, b, c (counter-clockwise from outside)
-  const double* tn;        // [n_tri][3] unit outward face normal
-  const int32_t* tid;      // [n_tri][6] vertex ids of a, b, c; edge ids of ab, bc, ca
-  const double* en;        // [n_edge][3] edge pseudonormal (sum of the two face normals)
-  const double* vn;        // [n_vert][3] vertex pseudonormal (angle-weighted normal sum)
-  const BvhNode* nodes;
+  TC_GLOBAL const double* tv;        // [n_tri][9] corners a, b, c (counter-clockwise from outside)
+  TC_GLOBAL const double* tn;        // [n_tri][3] unit outward face normal
+  TC_GLOBAL const int32_t* tid;      // [n_tri][6] vertex ids of a, b, c; edge ids of ab, bc, ca
+  TC_GLOBAL const double* en;        // [n_edge][3] edge pseudonormal (sum of the two face normals)
+  TC_GLOBAL const double* vn;        // [n_vert][3] vertex pseudonormal (angle-weighted normal sum)
+  TC_GLOBAL const BvhNode* nodes;
   // vertex-face and edge-edge pairs (mesh_contact 2)
-  const double* mv;        // [n_vert][3] vertex positions
-  const double* va;        // [n_vert] a third of the area of the vertex's triangles
-  const int32_t* me;       // [n_edge][2] edge end vertex ids
-  const double* mel;       // [n_edge] edge length
-  const uint8_t* own;      // [n_tri] bit k: this triangle owns vertex tid[k], bit 3 + k: edge
+  TC_GLOBAL const double* mv;        // [n_vert][3] vertex positions
+  TC_GLOBAL const double* va;        // [n_vert] a third of the area of the vertex's triangles
+  TC_GLOBAL const int32_t* me;       // [n_edge][2] edge end vertex ids
+  TC_GLOBAL const double* mel;       // [n_edge] edge length
+  TC_GLOBAL const uint8_t* own;      // [n_tri] bit k: this triangle owns vertex tid[k], bit 3 + k: edge
                            // tid[3 + k] (each vertex and edge owned by its first triangle in
                            // leaf order, so a traversal meets it once)
 };
@@ -181,82 +191,82 @@ struct EnvDesc {
   int32_t n_vt, n_tt, n_ct, n_st, n_at, n_te, n_spt;   // tiles per kernel class
   int32_t n_pt;              // pair tiles over S + Se surface primitives (mesh_contact 2, else 0)
   // resident inputs
-  const double* X;
-  double* x;
-  double* v;
-  const int32_t* tets;       // [T][4]
-  const void* Dminv;         // real [T][9]
-  const void* vol;           // real [T]
-  const int8_t* mat;         // [T] material index or null
-  const double* mass;        // [V]
-  const uint8_t* fixed;      // [V]
-  const int32_t* cand;       // [C]
-  const int32_t* cand_of_vert;  // [V], -1 if not a candidate
-  const double* cand_area;   // [C] rest barrier weight
-  const int32_t* tris;       // [S][3]
-  const int32_t* parent;     // [S]
-  const uint8_t* is_top;     // [S]
-  const int32_t* ctri_ptr;   // [C+1] triangles of each candidate: incident contact-face tris, or
+  TC_GLOBAL const double* X;
+  TC_GLOBAL double* x;
+  TC_GLOBAL double* v;
+  TC_GLOBAL const int32_t* tets;       // [T][4]
+  TC_GLOBAL const void* Dminv;         // real [T][9]
+  TC_GLOBAL const void* vol;           // real [T]
+  TC_GLOBAL const int8_t* mat;         // [T] material index or null
+  TC_GLOBAL const double* mass;        // [V]
+  TC_GLOBAL const uint8_t* fixed;      // [V]
+  TC_GLOBAL const int32_t* cand;       // [C]
+  TC_GLOBAL const int32_t* cand_of_vert;  // [V], -1 if not a candidate
+  TC_GLOBAL const double* cand_area;   // [C] rest barrier weight
+  TC_GLOBAL const int32_t* tris;       // [S][3]
+  TC_GLOBAL const int32_t* parent;     // [S]
+  TC_GLOBAL const uint8_t* is_top;     // [S]
+  TC_GLOBAL const int32_t* ctri_ptr;   // [C+1] triangles of each candidate: incident contact-face tris, or
                              // all incident surface tris for a side-face vertex
-  const int32_t* ctri_idx;
-  const int32_t* col;        // [V][W] block column of each stored block, -1 = empty
-  const int32_t* cptr;       // [V*W+1] contribution ranges per (row, slot)
-  const uint32_t* clist;     // (tet << 4) | (a << 2) | b
-  const int32_t* dptr;       // [V+1] diagonal-stream range of each row
-  const int32_t* eptr;       // [V_E+1] edge-stream range of each edge
-  const int32_t* eitem;      // [V_E][2] blocks (i, slot of j), (j, slot of i)
-  const int32_t* cpos;       // [T][10] stream positions: 4 diagonal, 6 edge blocks
-  const int32_t* sedge;      // [Se][2] surface edges (i < j), ascending
-  const double* sedge_len0;  // [Se] rest length
-  const int32_t* sedge_adj;  // [Se][2] its surface triangles: tri << 3 | pair block (3 ab, 4 bc, 5 ca)
-  const int32_t* edge_sedge; // [V_E] surface edge of each unique edge, -1 if interior
-  const int32_t* vp_ptr;     // [C+1] surface primitives of each contact vertex
-  const int32_t* vp_idx;     //   primitive << 2 | its local vertex (triangles j, edges S + f)
+  TC_GLOBAL const int32_t* ctri_idx;
+  TC_GLOBAL const int32_t* col;        // [V][W] block column of each stored block, -1 = empty
+  TC_GLOBAL const int32_t* cptr;       // [V*W+1] contribution ranges per (row, slot)
+  TC_GLOBAL const uint32_t* clist;     // (tet << 4) | (a << 2) | b
+  TC_GLOBAL const int32_t* dptr;       // [V+1] diagonal-stream range of each row
+  TC_GLOBAL const int32_t* eptr;       // [V_E+1] edge-stream range of each edge
+  TC_GLOBAL const int32_t* eitem;      // [V_E][2] blocks (i, slot of j), (j, slot of i)
+  TC_GLOBAL const int32_t* cpos;       // [T][10] stream positions: 4 diagonal, 6 edge blocks
+  TC_GLOBAL const int32_t* sedge;      // [Se][2] surface edges (i < j), ascending
+  TC_GLOBAL const double* sedge_len0;  // [Se] rest length
+  TC_GLOBAL const int32_t* sedge_adj;  // [Se][2] its surface triangles: tri << 3 | pair block (3 ab, 4 bc, 5 ca)
+  TC_GLOBAL const int32_t* edge_sedge; // [V_E] surface edge of each unique edge, -1 if interior
+  TC_GLOBAL const int32_t* vp_ptr;     // [C+1] surface primitives of each contact vertex
+  TC_GLOBAL const int32_t* vp_idx;     //   primitive << 2 | its local vertex (triangles j, edges S + f)
   // outputs
-  void* sigma;               // real [T][6]
-  void* traction;            // real [S][3]
-  void* pressure;            // real [S]
-  void* tangential;          // real [S][3]
-  void* tri_area;            // real [S]
-  void* tri_normal;          // real [S][3]
-  double* tri_cross;         // [S][3] e1 x e2 (current)
-  double* c_force;           // [C][3]
-  double* c_normal;
-  double* c_area;
-  double* c_fn;
-  double* c_ft;
-  double* c_press;
-  double* reaction;          // [3]
-  double* traction_sum;      // [3]
+  TC_GLOBAL void* sigma;               // real [T][6]
+  TC_GLOBAL void* traction;            // real [S][3]
+  TC_GLOBAL void* pressure;            // real [S]
+  TC_GLOBAL void* tangential;          // real [S][3]
+  TC_GLOBAL void* tri_area;            // real [S]
+  TC_GLOBAL void* tri_normal;          // real [S][3]
+  TC_GLOBAL double* tri_cross;         // [S][3] e1 x e2 (current)
+  TC_GLOBAL double* c_force;           // [C][3]
+  TC_GLOBAL double* c_normal;
+  TC_GLOBAL double* c_area;
+  TC_GLOBAL double* c_fn;
+  TC_GLOBAL double* c_ft;
+  TC_GLOBAL double* c_press;
+  TC_GLOBAL double* reaction;          // [3]
+  TC_GLOBAL double* traction_sum;      // [3]
   // step scratch
-  void* Ke;                  // real [4 T][KC] diagonal stream, then [6 T][KC] edge stream
-  void* A;                   // real [V][W][9] row-major 3x3 blocks
-  double* xn;                // Newton iterate [V][3]
-  double* xhat;
-  double* g;                 // gradient [V][3]
-  void* d;                   // real [V][3] Newton direction (CG solution)
-  double* r;                 // CG residual
-  void* z;                   // real
-  void* p0;                  // real, ping-pong search directions
-  void* p1;
-  void* q;                   // real, A p
-  void* Pinv;                // real [V][6] symmetric preconditioner blocks
-  double* gb;                // [C][3] barrier gradient
-  double* Hb;                // [C][6] projected barrier Hessian
-  double* fric;              // [MAX_IND][C][FRIC_STRIDE] lagged friction (friction on)
-  double* part_rz;           // [n_vt]
-  double* part_pq;           // [n_spt]
-  double* part_g2;           // [n_vt]
-  double* part_e;            // [n_te + n_vt + n_ct + n_pt]
-  double* part_dir;          // [2 n_vt]
-  double* part_filt;         // [n_ct + n_pt]
-  double* part_c3;           // [3 n_ct]
-  double* part_s3;           // [3 n_st]
-  double* prec;              // [S + Se][PREC] pair records (mesh_contact 2)
-  int32_t* pflag;            // [S + Se] 1 where the record holds pairs
-  EnvState* st;
-  const EnvPose* pose;
-  const DevMesh* meshes;     // [MAX_MESHES] the context's rigid meshes
+  TC_GLOBAL void* Ke;                  // real [4 T][KC] diagonal stream, then [6 T][KC] edge stream
+  TC_GLOBAL void* A;                   // real [V][W][9] row-major 3x3 blocks
+  TC_GLOBAL double* xn;                // Newton iterate [V][3]
+  TC_GLOBAL double* xhat;
+  TC_GLOBAL double* g;                 // gradient [V][3]
+  TC_GLOBAL void* d;                   // real [V][3] Newton direction (CG solution)
+  TC_GLOBAL double* r;                 // CG residual
+  TC_GLOBAL void* z;                   // real
+  TC_GLOBAL void* p0;                  // real, ping-pong search directions
+  TC_GLOBAL void* p1;
+  TC_GLOBAL void* q;                   // real, A p
+  TC_GLOBAL void* Pinv;                // real [V][6] symmetric preconditioner blocks
+  TC_GLOBAL double* gb;                // [C][3] barrier gradient
+  TC_GLOBAL double* Hb;                // [C][6] projected barrier Hessian
+  TC_GLOBAL double* fric;              // [MAX_IND][C][FRIC_STRIDE] lagged friction (friction on)
+  TC_GLOBAL double* part_rz;           // [n_vt]
+  TC_GLOBAL double* part_pq;           // [n_spt]
+  TC_GLOBAL double* part_g2;           // [n_vt]
+  TC_GLOBAL double* part_e;            // [n_te + n_vt + n_ct + n_pt]
+  TC_GLOBAL double* part_dir;          // [2 n_vt]
+  TC_GLOBAL double* part_filt;         // [n_ct + n_pt]
+  TC_GLOBAL double* part_c3;           // [3 n_ct]
+  TC_GLOBAL double* part_s3;           // [3 n_st]
+  TC_GLOBAL double* prec;              // [S + Se][PREC] pair records (mesh_contact 2)
+  TC_GLOBAL int32_t* pflag;            // [S + Se] 1 where the record holds pairs
+  TC_GLOBAL EnvState* st;
+  TC_GLOBAL const EnvPose* pose;
+  TC_GLOBAL const DevMesh* meshes;     // [MAX_MESHES] the context's rigid meshes
   // material table (Eq. 1) and parameters
   // cshift = lam (alpha - 1): mu for the rest-stable shift, 0 for alpha = 1
   double mu[MAX_MAT], lam[MAX_MAT], alpha[MAX_MAT], rho[MAX_MAT], cshift[MAX_MAT];
