@@ -2509,6 +2509,186 @@ __device__ __forceinline__ void cg_update_tile(const Tile tl, const EnvDesc* env
   if (threadIdx.x == 0) *part_rz = rzn;
 }
 
+// The whole CG of a small pad (cg_small_rows: rows of at most 16 blocks) in one
+// block of 16 waves: thread i owns row i and keeps its r, d, z and
+// preconditioner in registers, p and q go through LDS, groups of 16 lanes take
+// the rows' products.  In float the first CG_SMALL_RES row steps of a group
+// keep their blocks in registers; the others' are read each iteration, from
+// the XCD's L2, one step ahead of their product.
+//
+// Rows, partial sums and their order are those of the launched kernels with
+// blocks of 256: four waves stand for a block, so that both give the same bits
+// and the choice can look at what else is in the launch.
+//
+// Why: such a pad's launched iteration is two chains of loads and two launch
+// gaps, about 10 us at any size below some 10k tets; here it is the products
+// (one CU reads 64 B/clk from L2) and four barriers.  Two steps of a pad,
+// launched -> here: float, 400 rows 6.0 -> 3.8 ms, 648 rows 7.9 -> 5.2, 1001
+// rows 9.5 -> 7.6; double, 400 rows 9.1 -> 7.0, 648 rows 12.6 -> 10.7, 780
+// rows 11.9 -> 12.3.  Of 40 pads: float, 400 rows 17.9 -> 13.0, 648 rows 21.3
+// -> 18.2, 1001 rows 25.7 -> 25.4; double, 400 rows 29.5 -> 25.1, 495 rows 64
+// -> 50, 780 rows 37.6 -> 47.7.  Beside larger pads the launched iterations
+// carry the small ones along for nothing.
+template <typename R> constexpr int CG_SMALL_RES = sizeof(R) == 4 ? 4 : 0;
+
+template <typename R>
+__global__ void __launch_bounds__(1024) k_cg_small(const Tile* tiles, const EnvDesc* envs) {
+  constexpr int RES = CG_SMALL_RES<R>, STEPS = 4 * ((CG_SMALL + 255) / 256);
+  __shared__ R sp[3 * CG_SMALL], sq[3 * CG_SMALL];
+  __shared__ double s_pq[STEPS / 4][16], s_rz[16];
+  // column of each lane's slot in the row steps beyond the resident ones
+  __shared__ unsigned short scol[STEPS - RES][1024];
+  const Tile tl = tiles[blockIdx.x];
+  const EnvDesc& E = envs[tl.env];
+  gptr<EnvState> S = E.st;
+  const CgState c = cg_state((gptr<const EnvState>)S, 1);
+  if (!c.go) return;                    // (this block alone writes the pad's state)
+  const int V = E.V, W = E.W, i = threadIdx.x;
+  const bool in = i < V;
+  const int lane = threadIdx.x & 15, g = threadIdx.x >> 4;
+  gptr<const R> A = (gptr<const R>)E.A;
+  // step k of group g: 4 tiles of 64 rows at a time, 16 groups to a tile, its
+  // rows 16 apart (the launched kernel's order)
+  auto row_of = [&](int k) { return 256 * (k >> 2) + 64 * (g >> 4) + 16 * (k & 3) + (g & 15); };
+  auto column = [&](int k) {            // -1: no block
+    const int row = row_of(k);
+    const int j = E.col[min(row, V - 1) * W + min(lane, W - 1)];
+    return row < V && lane < W ? j : -1;
+  };
+  auto load = [&](int k, int j, R (&a)[9]) {
+    gptr<const R> As = A + 9 * (j >= 0 ? row_of(k) * W + lane : 0);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) a[q] = As[q];
+  };
+  const int steps = 4 * ((V + 255) / 256);
+  int col[RES > 0 ? RES : 1];
+  R blk[RES > 0 ? RES : 1][9];
+#pragma unroll
+  for (int k = 0; k < RES; ++k) {       // (steps >= 4)
+    col[k] = column(k);
+    load(k, col[k], blk[k]);
+  }
+  for (int k = RES; k < steps; ++k) scol[k - RES][threadIdx.x] = (unsigned short)column(k);
+  auto column_of = [&](int k) { return (int)(short)scol[k - RES][threadIdx.x]; };
+  const size_t row = in ? i : 0;
+  gptr<R> gd = (gptr<R>)E.d + 3 * row, gz = (gptr<R>)E.z + 3 * row, gp = (gptr<R>)E.p1 + 3 * row;
+  gptr<double> gr = E.r + 3 * row;
+  gptr<const R> gP = (gptr<const R>)E.Pinv + 6 * row;
+  R d[3], z[3], p[3], Pi[6];
+  double r[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) { d[q] = gd[q]; z[q] = gz[q]; p[q] = gp[q]; r[q] = gr[q]; }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) Pi[q] = gP[q];
+  // partials 0 .. n - 1 as PartialSum adds them (n <= 16)
+  const int n_vt = (V + 255) / 256, n_pt = (V + 63) / 64;
+  auto fold = [&](const double* w, int n) {     // of four waves' sums each
+    return row_sum16(lane < n ? ((w[4 * lane] + w[4 * lane + 1]) + w[4 * lane + 2]) + w[4 * lane + 3] : 0.0);
+  };
+  double rz = row_sum16(lane < n_vt ? E.part_rz[lane] : 0.0);
+  int it = c.it;
+  const double gdp = it + 1 < 0 ? row_sum16(lane < n_vt ? E.part_dir[lane] : 0.0) : 0.0;
+  double rz0 = c.rz0, tol2 = c.tol2, rzp = c.rzp;
+  int breakdown = c.breakdown;
+  __syncthreads();                      // all of the state is read before any of it is written
+  for (;;) {
+    ++it;
+    const bool first = it < 0 || (it == 0 && !c.warm);
+    if (first) {
+      rz0 = rz;
+      tol2 = cg_tol2_of(E, (const EnvState*)S, rz);
+    }
+    if (it >= 0 && (it >= E.max_cg || !(rz > tol2 * rz0) || breakdown)) break;
+    const R beta = (R)(it < 0 ? 1.0 : it == 0 ? 0.0 : rz / rzp);
+    rzp = it < 0 ? gdp : rz;
+    if (in) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        p[q] = z[q] + beta * p[q];
+        sp[3 * i + q] = p[q];
+      }
+    }
+    __syncthreads();
+    double pq = 0.0;
+    auto product = [&](int k, int j, const R (&a)[9]) {
+      if (__any(j >= 0)) {              // (the wave's rows may all lie past the pad's)
+        const R* pj = sp + 3 * max(j, 0);
+        const R p0 = pj[0], p1 = pj[1], p2 = pj[2];
+        const bool ok = j >= 0;
+        const R y0 = row_sum16(ok ? a[0] * p0 + a[1] * p1 + a[2] * p2 : R(0));
+        const R y1 = row_sum16(ok ? a[3] * p0 + a[4] * p1 + a[5] * p2 : R(0));
+        const R y2 = row_sum16(ok ? a[6] * p0 + a[7] * p1 + a[8] * p2 : R(0));
+        if (lane == 0 && ok) {          // slot 0 is the diagonal: pj is the row's own p
+          R* qo = sq + 3 * row_of(k);
+          qo[0] = y0; qo[1] = y1; qo[2] = y2;
+          pq += (double)p0 * y0 + (double)p1 * y1 + (double)p2 * y2;
+        }
+      }
+      if ((k & 3) == 3) {               // a tile's four rows a group are done
+        pq = wave_reduce(pq, OpSum());
+        if ((threadIdx.x & 63) == 0) s_pq[k >> 2][threadIdx.x >> 6] = pq;
+        pq = 0.0;
+      }
+    };
+#pragma unroll
+    for (int k = 0; k < RES; ++k) product(k, col[k], blk[k]);
+    if (RES < steps) {                  // the next step's blocks on their way during each product
+      R a[9], b[9];
+      int ja = column_of(RES), jb;
+      load(RES, ja, a);
+      for (int k = RES; k < steps; k += 2) {    // (steps - RES is even)
+        jb = column_of(k + 1);
+        load(k + 1, jb, b);
+        product(k, ja, a);
+        if (k + 2 < steps) {
+          ja = column_of(k + 2);
+          load(k + 2, ja, a);
+        }
+        product(k + 1, jb, b);
+      }
+    }
+    __syncthreads();
+    const double pAp = fold(&s_pq[0][0], n_pt);
+    double alpha = rzp / pAp;
+    if (!(pAp > 0.0) || !isfinite(alpha)) {
+      alpha = 0.0;
+      if (it >= 0) breakdown = 1;
+    }
+    double rzn = 0.0;
+    if (in) {
+      const R al = (R)alpha;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        d[q] = d[q] + al * p[q];
+        r[q] -= alpha * (double)sq[3 * i + q];
+      }
+      const R r0 = (R)r[0], r1 = (R)r[1], r2 = (R)r[2];
+      z[0] = Pi[0] * r0 + Pi[1] * r1 + Pi[2] * r2;
+      z[1] = Pi[1] * r0 + Pi[3] * r1 + Pi[4] * r2;
+      z[2] = Pi[2] * r0 + Pi[4] * r1 + Pi[5] * r2;
+      rzn = r[0] * (double)z[0] + r[1] * (double)z[1] + r[2] * (double)z[2];
+    }
+    rzn = wave_reduce(rzn, OpSum());
+    if ((threadIdx.x & 63) == 0) s_rz[threadIdx.x >> 6] = rzn;
+    __syncthreads();
+    rz = fold(s_rz, n_vt);
+  }
+  if (in) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) gd[q] = d[q];
+  }
+  if (i == 0) {
+    S->stage = ST_CG;
+    S->rz0 = rz0;
+    S->cg_tol2 = tol2;
+    S->breakdown = breakdown;
+    S->cg_stop[0] = S->cg_stop[1] = 1;
+    S->cg_done = 1;
+    S->cg_iters = it;
+    S->cg_small_its += it + c.warm;
+  }
+}
+
 // Optional self-timing of a launch on the GPU wall clock: every block stores
 // its start and end clock in its own pair of cells (plain stores, no
 // atomics); the host takes the earliest start and the latest end.
@@ -3226,6 +3406,9 @@ hipError_t launch_typed(KernelId id, const LaunchArgs& a) {
     case KernelId::cg_update:
       if (a.clock) TC_LAUNCH((k_cg_update<R, true>), a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs, a.parity, a.clock);
       else TC_LAUNCH((k_cg_update<R, false>), a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs, a.parity, nullptr);
+      break;
+    case KernelId::cg_small:
+      if (a.ntiles > 0) TC_GO(k_cg_small<R>, a.ntiles, 1024, a.stream, a.tiles, a.envs);
       break;
     case KernelId::newton_dir: TC_LAUNCH(k_newton_dir<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
     case KernelId::filter: TC_LAUNCH(k_filter<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;

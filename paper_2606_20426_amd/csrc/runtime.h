@@ -199,7 +199,9 @@ struct BatchPlan {
   Tile* d_tiles = nullptr;
   size_t dev_bytes = 0;
   // PAIR: surface triangles and edges (mesh_contact 2)
-  enum Cls { VERT, TET, CAND, SURF, ASM, ENERGY, SPMV, PAIR, NCLS };
+  // SMALL: one block per pad whose CG can run in one
+  enum Cls { VERT, TET, CAND, SURF, ASM, ENERGY, SPMV, PAIR, SMALL, NCLS };
+  static int tiles_of(int cls, const EnvDesc& E);
   int lpr = 0;                       // SpMV lanes per row
   int off[NCLS] = {0}, cnt[NCLS] = {0};
   std::vector<EnvDesc> h_desc;
@@ -287,6 +289,7 @@ struct Runner {
   struct View {
     const Tile* t[BatchPlan::NCLS];
     int c[BatchPlan::NCLS];
+    int n;                   // pads
     bool full;
   };
   // mask: bit c set for each kernel class c to list (the others stay

@@ -509,6 +509,22 @@ void free_lanes(tc_context* ctx) {
   ctx->lanes.clear();
 }
 
+// Tiles of one pad in a kernel class.
+int BatchPlan::tiles_of(int cls, const EnvDesc& E) {
+  switch (cls) {
+    case VERT: return E.n_vt;
+    case TET: return E.n_tt;
+    case CAND: return E.n_ct;
+    case SURF: return E.n_st;
+    case ASM: return E.n_at;
+    case ENERGY: return E.n_te + E.n_vt + E.n_ct;
+    case SPMV: return E.n_spt;
+    case PAIR: return E.n_pt;
+    case SMALL: return E.small ? 1 : 0;
+    default: return 0;
+  }
+}
+
 tc_status build_plan(tc_context* ctx, int n, tc_pad* const* pads, const int* slots, const SlotPool& pool,
                      std::unique_ptr<BatchPlan>& out, hipStream_t stream) {
   if (!stream) stream = ctx->stream;
@@ -549,26 +565,20 @@ tc_status build_plan(tc_context* ctx, int n, tc_pad* const* pads, const int* slo
     E.n_te = cdiv(p->T, BV);
     E.n_spt = cdiv(p->V, rows_spmv);
     E.n_pt = E.prec ? cdiv((int64_t)p->S + p->Se, BV) : 0;
+    // (its sums are those of launched blocks of 256)
+    E.small = P->lpr == 16 && BV == 256 && ctx->spmv_block == 256 && cg_small_rows(p->V, p->W, p->fp64);
     E.st = pool.d_state + slots[i];
     E.pose = pool.d_pose + slots[i];
     P->h_desc[i] = E;
   }
-  auto add_cls = [&](BatchPlan::Cls c, auto count_of) {
+  for (int c = 0; c < BatchPlan::NCLS; ++c) {
     P->off[c] = (int)tiles.size();
     for (int i = 0; i < n; ++i) {
-      const int k = count_of(P->h_desc[i]);
+      const int k = BatchPlan::tiles_of(c, P->h_desc[i]);
       for (int t = 0; t < k; ++t) tiles.push_back(Tile{i, t});
     }
     P->cnt[c] = (int)tiles.size() - P->off[c];
-  };
-  add_cls(BatchPlan::VERT, [](const EnvDesc& E) { return E.n_vt; });
-  add_cls(BatchPlan::TET, [](const EnvDesc& E) { return E.n_tt; });
-  add_cls(BatchPlan::CAND, [](const EnvDesc& E) { return E.n_ct; });
-  add_cls(BatchPlan::SURF, [](const EnvDesc& E) { return E.n_st; });
-  add_cls(BatchPlan::ASM, [](const EnvDesc& E) { return E.n_at; });
-  add_cls(BatchPlan::ENERGY, [](const EnvDesc& E) { return E.n_te + E.n_vt + E.n_ct; });
-  add_cls(BatchPlan::SPMV, [](const EnvDesc& E) { return E.n_spt; });
-  add_cls(BatchPlan::PAIR, [](const EnvDesc& E) { return E.n_pt; });
+  }
   // buffers of the replaced plan are taken over when large enough (its graph
   // executable, which holds their addresses, is destroyed with it below);
   // new ones get 25 % headroom
@@ -669,6 +679,7 @@ Runner::View Runner::view(bool (*pred)(const EnvState&), unsigned mask, bool cop
   View v{};
   int nm = 0;
   for (int i = 0; i < n; ++i) nm += pred(state(i));
+  v.n = nm;
   v.full = nm == n;
   if (v.full) {
     for (int c = 0; c < BatchPlan::NCLS; ++c) {
@@ -688,11 +699,7 @@ Runner::View Runner::view(bool (*pred)(const EnvState&), unsigned mask, bool cop
     int k = start;
     for (int i = 0; i < n; ++i) {
       if (!pred(state(i))) continue;
-      const EnvDesc& E = P->h_desc[i];
-      const int cnt = c == BatchPlan::VERT ? E.n_vt : c == BatchPlan::TET ? E.n_tt : c == BatchPlan::CAND ? E.n_ct
-                    : c == BatchPlan::SURF ? E.n_st : c == BatchPlan::ASM ? E.n_at
-                    : c == BatchPlan::ENERGY ? E.n_te + E.n_vt + E.n_ct
-                    : c == BatchPlan::PAIR ? E.n_pt : E.n_spt;
+      const int cnt = BatchPlan::tiles_of(c, P->h_desc[i]);
       if (k + cnt > P->ctiles_cap) {   // cannot happen (4x capacity); never launch a truncated list
         ring_overflow = true;
         break;
@@ -745,25 +752,31 @@ bool Runner::any_pairs(bool (*pred)(const EnvState&)) const {
 }
 
 tc_status Runner::cg_chunk(int M, const View& v) {
+  // with small pads only, one block each takes their CG to its end; beside
+  // larger ones the launched iterations carry them along
+  if (v.c[BatchPlan::SMALL] == v.n) {
+    launch_v(KernelId::cg_small, v, BatchPlan::SMALL);
+    return TC_OK;
+  }
+  auto iterations = [&] {
+    for (int k = 0; k < M; ++k) {
+      launch_v(KernelId::cg_spmv, v, BatchPlan::SPMV, k & 1);
+      launch_v(KernelId::cg_update, v, BatchPlan::VERT, k & 1);
+    }
+  };
   if (v.full && ctx->use_graphs && !ctx->timing) {
     if (!P->cg_exec || P->graph_M != M) {
       if (P->cg_exec) { (void)hipGraphExecDestroy(P->cg_exec); P->cg_exec = nullptr; }
       if (P->cg_graph) { (void)hipGraphDestroy(P->cg_graph); P->cg_graph = nullptr; }
       TC_HIP(hipStreamBeginCapture(strm(), hipStreamCaptureModeThreadLocal));
-      for (int k = 0; k < M; ++k) {
-        launch_v(KernelId::cg_spmv, v, BatchPlan::SPMV, k & 1);
-        launch_v(KernelId::cg_update, v, BatchPlan::VERT, k & 1);
-      }
+      iterations();
       TC_HIP(hipStreamEndCapture(strm(), &P->cg_graph));
       TC_HIP(hipGraphInstantiate(&P->cg_exec, P->cg_graph, nullptr, nullptr, 0));
       P->graph_M = M;
     }
     TC_HIP(hipGraphLaunch(P->cg_exec, strm()));
   } else {
-    for (int k = 0; k < M; ++k) {
-      launch_v(KernelId::cg_spmv, v, BatchPlan::SPMV, k & 1);
-      launch_v(KernelId::cg_update, v, BatchPlan::VERT, k & 1);
-    }
+    iterations();
   }
   return TC_OK;
 }
@@ -908,7 +921,7 @@ tc_status Runner::round(int M, int K, bool serve) {
   const unsigned mD = 1u << B::VERT | 1u << B::CAND | 1u << B::PAIR;
   const unsigned mL = 1u << B::ENERGY | 1u << B::PAIR | 1u << B::VERT;
   const unsigned mA = 1u << B::TET | 1u << B::PAIR | 1u << B::CAND | 1u << B::VERT | 1u << B::ASM;
-  const unsigned mC = 1u << B::SPMV | 1u << B::VERT;
+  const unsigned mC = 1u << B::SPMV | 1u << B::VERT | 1u << B::SMALL;
   const bool anyD = any(dir_pending), anyL = any(turning), anyA = any(starting);
   std::vector<char> was_dir;
   if (debug)
@@ -997,10 +1010,12 @@ static double kernel_bytes(KernelId k, const tc_pad* p) {
 }
 
 void account_bytes(tc_context* ctx, const tc_pad* pad, const EnvState& S) {
-  const double nt = S.newton_iters, cg = S.cg_total;
+  const double nt = S.newton_iters, small = S.cg_small_its, cg = S.cg_total - small;
   auto add = [&](KernelId k, double count) { ctx->timers[(int)k].bytes += count * kernel_bytes(k, pad); };
   add(KernelId::cg_spmv, cg);
   add(KernelId::cg_update, cg);
+  ctx->timers[(int)KernelId::cg_small].bytes +=
+      small * (kernel_bytes(KernelId::cg_spmv, pad) + kernel_bytes(KernelId::cg_update, pad));
   add(KernelId::element, nt);
   add(KernelId::asm_diag, nt);
   add(KernelId::asm_off, nt);

@@ -35,6 +35,15 @@ constexpr int KC = 9;
 // rows handled by each lane group of the vectorised SpMV per tile
 constexpr int SPMV_ROWS_PER_GROUP = 4;
 
+// Pads whose CG can run in one block (k_cg_small): rows of at most 16 blocks,
+// and at most this many of them, one per thread of 16 waves.  In double one
+// CU's reads of the matrix cost more than launches beyond 640 rows (both
+// sides measured at the kernel).
+constexpr int CG_SMALL = 1024;
+__host__ __device__ constexpr bool cg_small_rows(int V, int W, bool fp64) {
+  return W <= 16 && V <= (fp64 ? 640 : CG_SMALL);
+}
+
 // offset of block (a, b), a <= b, inside the record; diagonal blocks hold
 // (xx, xy, xz, yy, yz, zz), off-diagonal blocks row-major 3x3
 __host__ __device__ constexpr int ke_block_offset(int a, int b) {
@@ -145,6 +154,7 @@ struct EnvState {
   int32_t newton_done;
   int32_t newton_iters;
   int32_t cg_total;
+  int32_t cg_small_its;    // of those, in one block (k_cg_small)
   int32_t ls_total;
   double final_step_inf;
   double reaction[3];
@@ -189,6 +199,7 @@ struct EnvDesc {
   int32_t V_E;               // unique edges (off-diagonal block pairs)
   int32_t Se;                // surface edges
   int32_t n_vt, n_tt, n_ct, n_st, n_at, n_te, n_spt;   // tiles per kernel class
+  int32_t small;             // its CG runs in one block (k_cg_small)
   int32_t n_pt;              // pair tiles over S + Se surface primitives (mesh_contact 2, else 0)
   // resident inputs
   TC_GLOBAL const double* X;

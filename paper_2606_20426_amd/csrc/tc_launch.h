@@ -35,6 +35,7 @@ enum class KernelId : int {
   pairs,
   pair_push,
   pair_apply,
+  cg_small,
   count
 };
 
@@ -44,7 +45,7 @@ inline const char* kernel_name(KernelId k) {
                                 "cg_spmv",    "cg_update",  "newton_dir", "filter",    "env_dir",
                                 "energy",     "env_ls",     "update",     "env_update", "sigma",     "traction",
                                 "contact",    "env_extract", "commit",     "pairs",     "pair_push",
-                                "pair_apply"};
+                                "pair_apply", "cg_small"};
   return names[static_cast<int>(k)];
 }
 
