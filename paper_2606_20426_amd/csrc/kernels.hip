@@ -810,23 +810,75 @@ __device__ double seg_seg(const double p0[3], const double p1[3], const double q
   return q;
 }
 
-// Leaves of M's hierarchy whose boxes meet [lo, hi]: leaf(s) per triangle
-// slot s.
+// Pair work is shared out over groups of PAIR_LANES lanes (a row of a wave),
+// one pad primitive to a group: its lanes test the nodes of a mesh's hierarchy
+// side by side, then the features of the leaves found.  Control flow is the
+// same for all lanes of a group, and a group's LDS is its own.
+struct PairWork {
+  int stack[PAIR_STACK];
+  int slots[PAIR_SLOTS];
+};
+
+// LDS writes of a wave's lanes are seen by its other lanes from here on.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Lanes of the group for which b holds.
+__device__ __forceinline__ unsigned group_mask(bool b) {
+  return (unsigned)(__ballot(b) >> (threadIdx.x & 48)) & 0xffffu;
+}
+
+// Leaves of M's hierarchy whose boxes meet [lo, hi]: leaf(n) for n >= 1 of
+// their triangle slots in W.slots, by the whole group.
+//
+// One thread to a primitive walked node by node, each a round trip to memory
+// (121 us an energy pass of 8 pads with 14k primitives, most of which meet
+// nothing); a group takes 16 nodes a round trip, so the walk is as long as the
+// hierarchy is deep.
 template <typename Leaf>
-__device__ void bvh_overlap(const DevMesh& M, const double lo[3], const double hi[3], Leaf&& leaf) {
-  int stack[BVH_STACK];
-  int sp = 0;
-  stack[sp++] = 0;
+__device__ __forceinline__ void bvh_overlap(const DevMesh& M, const double lo[3], const double hi[3], PairWork& W,
+                                            Leaf&& leaf) {
+  const int lane = threadIdx.x & (PAIR_LANES - 1);
+  const unsigned below = (1u << lane) - 1;
+  int sp = 1, ns = 0;
+  if (lane == 0) W.stack[0] = 0;
+  wave_sync();
   while (sp > 0) {
-    const BvhNode& nd = M.nodes[stack[--sp]];
-    if (nd.lo[0] > hi[0] || nd.hi[0] < lo[0] || nd.lo[1] > hi[1] || nd.hi[1] < lo[1] || nd.lo[2] > hi[2] ||
-        nd.hi[2] < lo[2])
-      continue;
-    if (nd.count > 0) {
-      for (int s = nd.first; s < nd.first + nd.count; ++s) leaf(s);
-    } else if (sp + 2 <= BVH_STACK) {
-      stack[sp++] = nd.first;
-      stack[sp++] = (int)(&nd - M.nodes) + 1;
+    // nodes taken at once: a wide front may not fill the stack; one at a time
+    // it grows by the depth of the hierarchy at most
+    const int n = max(min(min(PAIR_LANES, sp), PAIR_STACK - BVH_STACK - sp), 1);
+    const bool have = lane < n;
+    const int node = have ? W.stack[sp - 1 - lane] : 0;
+    sp -= n;
+    const BvhNode& nd = M.nodes[node];
+    const bool hit = have && !(nd.lo[0] > hi[0] || nd.hi[0] < lo[0] || nd.lo[1] > hi[1] || nd.hi[1] < lo[1] ||
+                               nd.lo[2] > hi[2] || nd.hi[2] < lo[2]);
+    const int first = nd.first, count = hit ? nd.count : -1;
+    const unsigned inner = group_mask(count == 0);
+    wave_sync();
+    if (count == 0) {
+      const int o = sp + 2 * __popc(inner & below);
+      if (o + 2 <= PAIR_STACK) {
+        W.stack[o] = first;
+        W.stack[o + 1] = node + 1;
+      }
+    }
+    sp = min(sp + 2 * __popc(inner), PAIR_STACK);
+    // the leaves' slots (at most MESH_LEAF = 4 each)
+    int o = ns;
+    for (int q = 1; q <= MESH_LEAF; ++q) {
+      const unsigned m = group_mask(count >= q);
+      o += __popc(m & below);
+      ns += __popc(m);
+    }
+    for (int q = 0; q < count; ++q) W.slots[o + q] = first + q;
+    wave_sync();
+    if (ns >= PAIR_LANES || (sp == 0 && ns > 0)) {
+      leaf(ns);
+      ns = 0;
+      wave_sync();
     }
   }
 }
@@ -843,136 +895,135 @@ __device__ __forceinline__ int prim_verts(const EnvDesc& E, int j, int vid[3]) {
     return 3;
   }
   const int f = j - E.S;
-  vid[0] = E.sedge[2 * f]; vid[1] = E.sedge[2 * f + 1]; vid[2] = -1;
+  vid[0] = E.sedge[2 * f]; vid[1] = vid[2] = E.sedge[2 * f + 1];
   return 2;
 }
 
 // Every pair of pad primitive j (vertices xw, world) with the mesh
-// indenters nearer than r[m]: fn(m, PairTerm).
-template <typename Fn>
-__device__ void visit_pairs(const EnvDesc& E, const EnvPose* P, int j, const double xw[3][3], const double* r,
-                            Fn&& fn) {
+// indenters nearer than rad(m): fn(m, hit, PairTerm), called by the whole group
+// whenever one of its lanes hit a pair.
+template <typename Rad, typename Fn>
+__device__ __forceinline__ void visit_pairs(const EnvDesc& E, const EnvPose* P, int j, const double xw[3][3],
+                                            PairWork& W, Rad&& rad, Fn&& fn) {
+  const int lane = threadIdx.x & (PAIR_LANES - 1);
   const bool tri = j < E.S;
-  const int nv = tri ? 3 : 2;
   const double len0 = tri ? 0.0 : E.sedge_len0[j - E.S];
   for (int m = 0; m < P->n_ind; ++m) {
     const DevIndenter& I = P->ind[m];
-    if (I.shape != TC_MESH || !(r[m] > 0.0)) continue;
+    const double r = rad(m);
+    if (I.shape != TC_MESH || !(r > 0.0)) continue;
     const DevMesh& M = E.meshes[I.reserved];
     double xl[3][3], lo[3], hi[3];
-    for (int k = 0; k < nv; ++k)
+    for (int k = 0; k < 3; ++k)
       for (int i = 0; i < 3; ++i)
         xl[k][i] = I.R[0 * 3 + i] * (xw[k][0] - I.c[0]) + I.R[1 * 3 + i] * (xw[k][1] - I.c[1]) +
                    I.R[2 * 3 + i] * (xw[k][2] - I.c[2]);
     for (int i = 0; i < 3; ++i) {
-      lo[i] = xl[0][i];
-      hi[i] = xl[0][i];
-      for (int k = 1; k < nv; ++k) { lo[i] = fmin(lo[i], xl[k][i]); hi[i] = fmax(hi[i], xl[k][i]); }
-      lo[i] -= r[m];
-      hi[i] += r[m];
+      lo[i] = fmin(fmin(xl[0][i], xl[1][i]), xl[2][i]) - r;
+      hi[i] = fmax(fmax(xl[0][i], xl[1][i]), xl[2][i]) + r;
     }
-    const double r2 = r[m] * r[m];
+    const double r2 = r * r;
     auto world = [&](const double* l, double* w) {
       for (int i = 0; i < 3; ++i) w[i] = I.R[i * 3 + 0] * l[0] + I.R[i * 3 + 1] * l[1] + I.R[i * 3 + 2] * l[2];
     };
-    auto outside = [&](const double* y) {
-      return y[0] < lo[0] || y[0] > hi[0] || y[1] < lo[1] || y[1] > hi[1] || y[2] < lo[2] || y[2] > hi[2];
-    };
-    bvh_overlap(M, lo, hi, [&](int s) {
+    // feature k of leaf slot s: fills pt and returns true when it is a pair
+    auto feature = [&](int s, int k, PairTerm& pt) {
       const unsigned own = M.own[s];
-      const int32_t* id = M.tid + 6 * (size_t)s;
-      for (int k = 0; k < 3; ++k) {
-        PairTerm pt;
-        double dl[3];
-        if (tri) {
-          if (!((own >> k) & 1u)) continue;
-          const int v = id[k];
-          const double* y = M.mv + 3 * (size_t)v;
-          if (outside(y)) continue;
-          const double d2 = pt_tri_lam(y, xl[0], xl[1], xl[2], pt.lam, dl);
-          if (!(d2 < r2)) continue;
-          pt.d = sqrt(d2);
-          pt.wt = M.va[v];
-          pt.m = 1.0;
-          pt.dm = 0.0;
-          pt.dc1[0] = pt.dc1[1] = pt.dc1[2] = 0.0;
-          pt.interior = pt.lam[0] > 0 && pt.lam[1] > 0 && pt.lam[2] > 0;
-          pt.w0 = y;
-          pt.w1 = nullptr;
-          pt.sep = 0.0;
-          if (pt.d > 0.0) {
-            const double iu = 1.0 / pt.d;
-            auto pr = [&](const double* q) { return (q[0] * dl[0] + q[1] * dl[1] + q[2] * dl[2]) * iu; };
-            pt.sep = pr(y) - fmax(fmax(pr(xl[0]), pr(xl[1])), pr(xl[2]));
-          }
-        } else {
-          if (!((own >> (3 + k)) & 1u)) continue;
-          const int e = id[3 + k];
-          const double* p0 = M.mv + 3 * (size_t)M.me[2 * e];
-          const double* p1 = M.mv + 3 * (size_t)M.me[2 * e + 1];
-          if (fmin(p0[0], p1[0]) > hi[0] || fmax(p0[0], p1[0]) < lo[0] || fmin(p0[1], p1[1]) > hi[1] ||
-              fmax(p0[1], p1[1]) < lo[1] || fmin(p0[2], p1[2]) > hi[2] || fmax(p0[2], p1[2]) < lo[2])
-            continue;
-          double sp, tp;
-          const double d2 = seg_seg(p0, p1, xl[0], xl[1], sp, tp, dl);
-          if (!(d2 < r2)) continue;
-          pt.d = sqrt(d2);
-          pt.lam[0] = 1.0 - tp; pt.lam[1] = tp; pt.lam[2] = 0.0;
-          const double le = M.mel[e];
-          pt.wt = 0.25 * le * len0;
-          double ev[3], fv[3], cr[3];
-          for (int i = 0; i < 3; ++i) { ev[i] = p1[i] - p0[i]; fv[i] = xl[1][i] - xl[0][i]; }
-          cr[0] = ev[1] * fv[2] - ev[2] * fv[1];
-          cr[1] = ev[2] * fv[0] - ev[0] * fv[2];
-          cr[2] = ev[0] * fv[1] - ev[1] * fv[0];
-          const double cc = cr[0] * cr[0] + cr[1] * cr[1] + cr[2] * cr[2];
-          const double c0 = 1e-3 * le * le * len0 * len0;
-          const double xq = cc / c0;
-          pt.m = xq < 1.0 ? (2.0 - xq) * xq : 1.0;
-          pt.dm = xq < 1.0 ? (2.0 - 2.0 * xq) / c0 : 0.0;
-          const double ee = ev[0] * ev[0] + ev[1] * ev[1] + ev[2] * ev[2];
-          const double ef = ev[0] * fv[0] + ev[1] * fv[1] + ev[2] * fv[2];
-          double dcl[3];
-          for (int i = 0; i < 3; ++i) dcl[i] = 2.0 * (ee * fv[i] - ef * ev[i]);
-          world(dcl, pt.dc1);
-          pt.interior = sp > 0.0 && sp < 1.0 && tp > 0.0 && tp < 1.0;
-          pt.w0 = p0;
-          pt.w1 = p1;
-          pt.sep = 0.0;
-          if (pt.d > 0.0) {
-            const double iu = 1.0 / pt.d;
-            auto pr = [&](const double* q) { return (q[0] * dl[0] + q[1] * dl[1] + q[2] * dl[2]) * iu; };
-            pt.sep = fmin(pr(p0), pr(p1)) - fmax(pr(xl[0]), pr(xl[1]));
-          }
+      if (!((own >> (tri ? k : 3 + k)) & 1u)) return false;
+      const int id = M.tid[6 * (size_t)s + (tri ? k : 3 + k)];
+      double dl[3];
+      if (tri) {
+        const double* y = M.mv + 3 * (size_t)id;
+        if (y[0] < lo[0] || y[0] > hi[0] || y[1] < lo[1] || y[1] > hi[1] || y[2] < lo[2] || y[2] > hi[2]) return false;
+        const double d2 = pt_tri_lam(y, xl[0], xl[1], xl[2], pt.lam, dl);
+        if (!(d2 < r2)) return false;
+        pt.d = sqrt(d2);
+        pt.wt = M.va[id];
+        pt.m = 1.0;
+        pt.dm = 0.0;
+        pt.dc1[0] = pt.dc1[1] = pt.dc1[2] = 0.0;
+        pt.interior = pt.lam[0] > 0 && pt.lam[1] > 0 && pt.lam[2] > 0;
+        pt.w0 = y;
+        pt.w1 = nullptr;
+        pt.sep = 0.0;
+        if (pt.d > 0.0) {
+          const double iu = 1.0 / pt.d;
+          auto pr = [&](const double* q) { return (q[0] * dl[0] + q[1] * dl[1] + q[2] * dl[2]) * iu; };
+          pt.sep = pr(y) - fmax(fmax(pr(xl[0]), pr(xl[1])), pr(xl[2]));
         }
-        world(dl, pt.diff);
-        const double id_ = pt.d > 0.0 ? 1.0 / pt.d : 0.0;
-        for (int i = 0; i < 3; ++i) pt.u[i] = pt.diff[i] * id_;
-        fn(m, pt);
+      } else {
+        const double* p0 = M.mv + 3 * (size_t)M.me[2 * id];
+        const double* p1 = M.mv + 3 * (size_t)M.me[2 * id + 1];
+        if (fmin(p0[0], p1[0]) > hi[0] || fmax(p0[0], p1[0]) < lo[0] || fmin(p0[1], p1[1]) > hi[1] ||
+            fmax(p0[1], p1[1]) < lo[1] || fmin(p0[2], p1[2]) > hi[2] || fmax(p0[2], p1[2]) < lo[2])
+          return false;
+        double sp, tp;
+        const double d2 = seg_seg(p0, p1, xl[0], xl[1], sp, tp, dl);
+        if (!(d2 < r2)) return false;
+        pt.d = sqrt(d2);
+        pt.lam[0] = 1.0 - tp; pt.lam[1] = tp; pt.lam[2] = 0.0;
+        const double le = M.mel[id];
+        pt.wt = 0.25 * le * len0;
+        double ev[3], fv[3], cr[3];
+        for (int i = 0; i < 3; ++i) { ev[i] = p1[i] - p0[i]; fv[i] = xl[1][i] - xl[0][i]; }
+        cr[0] = ev[1] * fv[2] - ev[2] * fv[1];
+        cr[1] = ev[2] * fv[0] - ev[0] * fv[2];
+        cr[2] = ev[0] * fv[1] - ev[1] * fv[0];
+        const double cc = cr[0] * cr[0] + cr[1] * cr[1] + cr[2] * cr[2];
+        const double c0 = 1e-3 * le * le * len0 * len0;
+        const double xq = cc / c0;
+        pt.m = xq < 1.0 ? (2.0 - xq) * xq : 1.0;
+        pt.dm = xq < 1.0 ? (2.0 - 2.0 * xq) / c0 : 0.0;
+        const double ee = ev[0] * ev[0] + ev[1] * ev[1] + ev[2] * ev[2];
+        const double ef = ev[0] * fv[0] + ev[1] * fv[1] + ev[2] * fv[2];
+        double dcl[3];
+        for (int i = 0; i < 3; ++i) dcl[i] = 2.0 * (ee * fv[i] - ef * ev[i]);
+        world(dcl, pt.dc1);
+        pt.interior = sp > 0.0 && sp < 1.0 && tp > 0.0 && tp < 1.0;
+        pt.w0 = p0;
+        pt.w1 = p1;
+        pt.sep = 0.0;
+        if (pt.d > 0.0) {
+          const double iu = 1.0 / pt.d;
+          auto pr = [&](const double* q) { return (q[0] * dl[0] + q[1] * dl[1] + q[2] * dl[2]) * iu; };
+          pt.sep = fmin(pr(p0), pr(p1)) - fmax(pr(xl[0]), pr(xl[1]));
+        }
+      }
+      world(dl, pt.diff);
+      const double id_ = pt.d > 0.0 ? 1.0 / pt.d : 0.0;
+      for (int i = 0; i < 3; ++i) pt.u[i] = pt.diff[i] * id_;
+      return true;
+    };
+    bvh_overlap(M, lo, hi, W, [&](int ns) {
+      for (int f0 = 0; f0 < 3 * ns; f0 += PAIR_LANES) {
+        const int f = f0 + lane;
+        PairTerm pt;
+        const bool hit = f < 3 * ns && feature(W.slots[f / 3], f % 3, pt);
+        if (group_mask(hit)) fn(m, hit, pt);
       }
     });
   }
 }
 
-// Loads pad primitive j's vertex positions x (+ al * d when d is given).
+// Loads pad primitive j's vertex positions x (+ al * d when d is given; an
+// edge's second vertex stands for its third too).
 template <typename R>
 __device__ __forceinline__ int prim_load(const EnvDesc& E, int j, const double* x, const R* d, double al, int vid[3],
                                          double xw[3][3]) {
   const int nv = prim_verts(E, j, vid);
-  for (int k = 0; k < nv; ++k)
+  for (int k = 0; k < 3; ++k)
     for (int c = 0; c < 3; ++c)
       xw[k][c] = x[3 * vid[k] + c] + (d ? al * (double)d[3 * vid[k] + c] : 0.0);
   return nv;
 }
 
-// Pair energy of primitive j at positions xw (barrier units: the h^2 factor
-// is the caller's); +inf for a touching pair.
-__device__ double prim_pair_energy(const EnvDesc& E, const EnvPose* P, int j, const double xw[3][3]) {
-  double r[MAX_IND];
-  for (int m = 0; m < MAX_IND; ++m) r[m] = E.dhat;
+// This lane's share of the pair energy of primitive j at positions xw (barrier
+// units: the h^2 factor is the caller's); +inf for a touching pair.
+__device__ __forceinline__ double prim_pair_energy(const EnvDesc& E, const EnvPose* P, int j, const double xw[3][3],
+                                                   PairWork& W) {
   double e = 0.0;
-  visit_pairs(E, P, j, xw, r, [&](int, const PairTerm& pt) {
-    if (pt.m > 0.0) e += E.kappa * pt.wt * E.dhat * pt.m * bar0(pt.d / E.dhat);
+  visit_pairs(E, P, j, xw, W, [&](int) { return E.dhat; }, [&](int, bool hit, const PairTerm& pt) {
+    if (hit && pt.m > 0.0) e += E.kappa * pt.wt * E.dhat * pt.m * bar0(pt.d / E.dhat);
   });
   return e;
 }
@@ -1444,10 +1495,10 @@ __global__ void __launch_bounds__(256) k_element(const Tile* tiles, int ntiles, 
 __device__ __forceinline__ bool extract_ok(const EnvState* S);
 
 template <typename R>
-__device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, const R* d, double span);
+__device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, const R* d, double span, PairWork& W);
 
 // Per surface primitive (pad triangles, then surface edges) of pads with
-// vertex-face / edge-edge pairs:
+// vertex-face / edge-edge pairs, a group of lanes each:
 //   mode 0: records at the Newton iterate (pads running), mode 1: at the
 //           extraction positions: gradient and Gauss-Newton blocks of the
 //           primitive's pairs within d_hat, flag 0 for a primitive without
@@ -1458,10 +1509,15 @@ __device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, con
 //   mode 3: the pairs' step bound along the Newton direction, partial
 //           minima after the contact vertices' in the filter partials.
 // The pair work has its own launches so that its traversal state does not
-// raise the register use of the energy and filter kernels.
-template <typename R>
-__global__ void k_pairs(const Tile* tiles, int ntiles, const EnvDesc* envs, int mode) {
+// raise the register use of the energy and filter kernels; the records, whose
+// pairs pass through LDS, have a kernel of their own, and the step bound
+// (BOUND) one of more registers.  What bounds them is the chain of loads from
+// a primitive through its hierarchy to its pairs: 16 primitives to a block
+// give most groups one primitive of work and every CU several blocks.
+template <typename R, bool BOUND>
+__global__ void __launch_bounds__(PAIR_BLOCK, BOUND ? 2 : 4) k_pairs(const Tile* tiles, int ntiles, const EnvDesc* envs, int mode) {
   __shared__ double sh[16];
+  __shared__ PairWork work[PAIR_PRIMS];
   const int t = xcd_tile(ntiles);
   if (t < 0) return;
   const Tile tl = tiles[t];
@@ -1469,64 +1525,107 @@ __global__ void k_pairs(const Tile* tiles, int ntiles, const EnvDesc* envs, int 
   const EnvState* S = E.st;
   const EnvPose* P = E.pose;
   if (!pair_active(E, P)) return;
-  const int j = tl.tile * blockDim.x + threadIdx.x;
-  if (mode >= 2) {
-    // block reductions: every thread of the block takes part
-    if (mode == 2 ? !searching(S) : mode == 4 ? !initialising(S) : !dir_ready(S)) return;
-    const bool in = j < E.S + E.Se;
-    if (mode == 3) {
-      double a = INFINITY;
-      if (in) a = fmin(prim_pair_bound<R>(E, P, j, (const R*)E.d, FILTER_SPAN), FILTER_SPAN);
-      a = block_reduce(a, OpMin(), sh);
-      if (threadIdx.x == 0) E.part_filt[E.n_ct + tl.tile] = a;
-      return;
-    }
-    double e = 0.0;
-    if (in) {
-      int vid[3];
-      double xw[3][3];
-      prim_load<R>(E, j, E.xn, mode == 2 ? (const R*)E.d : nullptr, mode == 2 ? S->ls_alpha : 0.0, vid, xw);
-      e = prim_pair_energy(E, P, j, xw);
-    }
-    e = block_reduce(e, OpSum(), sh);
-    if (threadIdx.x == 0) E.part_e[E.n_te + E.n_vt + E.n_ct + tl.tile] = e;
+  if (mode == 2 ? !searching(S) : mode == 4 ? !initialising(S) : !dir_ready(S)) return;
+  // block reductions: every thread of the block takes part
+  const int grp = threadIdx.x / PAIR_LANES, j = tl.tile * PAIR_PRIMS + grp;
+  const bool in = j < E.S + E.Se;
+  if (BOUND) {
+    double a = INFINITY;
+    if (in) a = fmin(prim_pair_bound<R>(E, P, j, (const R*)E.d, FILTER_SPAN, work[grp]), FILTER_SPAN);
+    a = block_reduce(a, OpMin(), sh);
+    if (threadIdx.x == 0) E.part_filt[E.n_ct + tl.tile] = a;
     return;
   }
+  double e = 0.0;
+  if (in) {
+    int vid[3];
+    double xw[3][3];
+    prim_load<R>(E, j, E.xn, mode == 2 ? (const R*)E.d : nullptr, mode == 2 ? S->ls_alpha : 0.0, vid, xw);
+    e = prim_pair_energy(E, P, j, xw, work[grp]);
+  }
+  e = block_reduce(e, OpSum(), sh);
+  if (threadIdx.x == 0) E.part_e[E.n_te + E.n_vt + E.n_ct + tl.tile] = e;
+}
+
+// What a pair adds to a record is a product of these (in LDS, from the lane
+// that found the pair to the lanes that sum the record's values).
+enum { PV_LAM = 0, PV_U = 3, PV_DC = 6, PV_G = 9, PV_M = 10, PV_H = 11, PV_N = 12 };
+
+__global__ void __launch_bounds__(PAIR_BLOCK) k_pair_records(const Tile* tiles, int ntiles, const EnvDesc* envs,
+                                                             int mode) {
+  __shared__ PairWork work[PAIR_PRIMS];
+  __shared__ double pairs[PAIR_PRIMS][PAIR_LANES][PV_N];
+  const int t = xcd_tile(ntiles);
+  if (t < 0) return;
+  const Tile tl = tiles[t];
+  const EnvDesc& E = envs[tl.env];
+  const EnvState* S = E.st;
+  const EnvPose* P = E.pose;
+  if (!pair_active(E, P)) return;
   if (mode == 0 ? !at_stage(S, ST_ASM) : !extract_ok(S)) return;
+  const int grp = threadIdx.x / PAIR_LANES, lane = threadIdx.x % PAIR_LANES, j = tl.tile * PAIR_PRIMS + grp;
   if (j >= E.S + E.Se) return;
-  const double* x = (mode == 1 && S->mode == 1) ? E.x : E.xn;
   int vid[3];
   double xw[3][3];
-  prim_load<double>(E, j, x, nullptr, 0.0, vid, xw);
-  double r[MAX_IND];
-  for (int m = 0; m < MAX_IND; ++m) r[m] = E.dhat;
+  prim_load<double>(E, j, (mode == 1 && S->mode == 1) ? E.x : E.xn, nullptr, 0.0, vid, xw);
+  // lane's values of the record: lane, lane + 16 and lane + 32 of the 9 of the
+  // gradient and the 6 x 6 of the blocks (0,0) (1,1) (2,2) (0,1) (1,2) (2,0)
+  constexpr int N = (PAIR_VALUES + PAIR_LANES - 1) / PAIR_LANES;
+  int a0[N], a1[N], u0[N], u1[N];
+  double acc[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const int v = lane + PAIR_LANES * q, b = (v - 9) / 6, c = (v - 9) % 6;
+    const bool grad = v < 9;
+    a0[q] = grad ? v / 3 : b % 3;
+    a1[q] = b < 3 ? b : (b - 2) % 3;
+    u0[q] = grad ? v % 3 : c < 3 ? 0 : c < 5 ? 1 : 2;
+    u1[q] = c < 3 ? c : c < 5 ? c - 2 : 2;
+    if (grad) a1[q] = u1[q] = 0;
+    acc[q] = 0.0;
+  }
   int n = 0;
-  // a primitive has few pairs: each adds straight into the record (cleared
-  // at the first), which keeps the 45 sums out of registers
-  double* rec = E.prec + (size_t)PREC * j;
-  visit_pairs(E, P, j, xw, r, [&](int, const PairTerm& pt) {
-    if (n++ == 0)
-      for (int q = 0; q < 45; ++q) rec[q] = 0.0;
-    const double s = pt.d / E.dhat;
-    const double w = E.kappa * pt.wt;
-    const double b0 = bar0(s), b1 = bar1(s), b2 = bar2(s);
-    for (int a = 0; a < 3; ++a)
+  visit_pairs(E, P, j, xw, work[grp], [&](int) { return E.dhat; }, [&](int, bool hit, const PairTerm& pt) {
+    const unsigned m = group_mask(hit);
+    if (hit) {
+      double* o = pairs[grp][__popc(m & ((1u << lane) - 1))];
+      const double s = pt.d / E.dhat;
+      const double w = E.kappa * pt.wt;
       for (int i = 0; i < 3; ++i) {
-        // w d_hat dm b sign(a) dc/dx_1 (edge-edge) + w m b' dd/dx_a
-        double ga = -w * pt.m * b1 * pt.lam[a] * pt.u[i];
-        if (pt.dm != 0.0 && a < 2) ga += w * E.dhat * pt.dm * b0 * (a == 1 ? 1.0 : -1.0) * pt.dc1[i];
-        rec[3 * a + i] += ga;
+        o[PV_LAM + i] = pt.lam[i];
+        o[PV_U + i] = pt.u[i];
+        o[PV_DC + i] = pt.dc1[i];
       }
-    // vertex pairs of the blocks (0,0) (1,1) (2,2) (0,1) (1,2) (2,0)
-    const double c2 = w * pt.m * b2 / E.dhat;
-    const double uu[6] = {pt.u[0] * pt.u[0], pt.u[0] * pt.u[1], pt.u[0] * pt.u[2],
-                          pt.u[1] * pt.u[1], pt.u[1] * pt.u[2], pt.u[2] * pt.u[2]};
-    const double la[6] = {pt.lam[0] * pt.lam[0], pt.lam[1] * pt.lam[1], pt.lam[2] * pt.lam[2],
-                          pt.lam[0] * pt.lam[1], pt.lam[1] * pt.lam[2], pt.lam[2] * pt.lam[0]};
-    for (int q = 0; q < 6; ++q)
-      for (int c = 0; c < 6; ++c) rec[9 + 6 * q + c] += c2 * la[q] * uu[c];
+      o[PV_G] = -w * pt.m * bar1(s);
+      o[PV_M] = pt.dm != 0.0 ? w * E.dhat * pt.dm * bar0(s) : 0.0;
+      o[PV_H] = w * pt.m * bar2(s) / E.dhat;
+    }
+    wave_sync();
+    const int k = __popc(m);
+    n += k;
+    for (int i = 0; i < k; ++i) {
+      const double* o = pairs[grp][i];
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const double la = o[PV_LAM + a0[q]], u = o[PV_U + u0[q]];
+        if (lane + PAIR_LANES * q < 9) {
+          // w d_hat dm b sign(a) dc/dx_1 (edge-edge) + w m b' dd/dx_a
+          double ga = o[PV_G] * la * u;
+          if (o[PV_M] != 0.0 && a0[q] < 2) ga += (a0[q] == 1 ? o[PV_M] : -o[PV_M]) * o[PV_DC + u0[q]];
+          acc[q] += ga;
+        } else {
+          acc[q] += o[PV_H] * (la * o[PV_LAM + a1[q]]) * (u * o[PV_U + u1[q]]);
+        }
+      }
+    }
+    wave_sync();
   });
-  E.pflag[j] = n > 0;
+  if (lane == 0) E.pflag[j] = n > 0;
+  if (n == 0) return;
+  double* rec = E.prec + (size_t)PREC * j;
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    if (lane + PAIR_LANES * q < PAIR_VALUES) rec[lane + PAIR_LANES * q] = acc[q];
 }
 
 // Outward direction of pad primitive j at positions x: a triangle's unit
@@ -1564,42 +1663,44 @@ __device__ __forceinline__ void prim_outward(const EnvDesc& E, int j, const doub
 // its length go to its record, and k_pair_apply moves each vertex by the
 // longest push asked of it.  mode 1 (after the last round): any pair still
 // on the inner side makes the start infeasible.
-__global__ void k_pair_push(const Tile* tiles, int ntiles, const EnvDesc* envs, int mode) {
+__global__ void __launch_bounds__(PAIR_BLOCK) k_pair_push(const Tile* tiles, int ntiles, const EnvDesc* envs,
+                                                          int mode) {
+  __shared__ PairWork work[PAIR_PRIMS];
   const int t = xcd_tile(ntiles);
   if (t < 0) return;
   const EnvDesc& E = envs[tiles[t].env];
   EnvState* S = E.st;
   const EnvPose* P = E.pose;
   if (!initialising(S) || !pair_active(E, P)) return;
-  const int j = tiles[t].tile * blockDim.x + threadIdx.x;
+  const int grp = threadIdx.x / PAIR_LANES, j = tiles[t].tile * PAIR_PRIMS + grp;
   if (j >= E.S + E.Se) return;
   int vid[3];
   double xw[3][3];
   prim_load<double>(E, j, E.xn, nullptr, 0.0, vid, xw);
-  double r[MAX_IND];
-  for (int m = 0; m < MAX_IND; ++m) r[m] = P->travel[m] + E.dhat;
   double n[3];
   prim_outward(E, j, E.xn, n);
   const double dsafe = 0.1 * E.dhat;
   const double below = mode == 0 ? dsafe * (1.0 - 1e-9) : 0.0;
   double sdmin = INFINITY;
-  int cnt = 0;
-  visit_pairs(E, P, j, xw, r, [&](int, const PairTerm& pt) {
-    if (!pt.interior) return;
+  visit_pairs(E, P, j, xw, work[grp], [&](int m) { return P->travel[m] + E.dhat; },
+              [&](int, bool hit, const PairTerm& pt) {
+    if (!hit || !pt.interior) return;
     const double sd = pt.diff[0] * n[0] + pt.diff[1] * n[1] + pt.diff[2] * n[2];
     // the closest points' vector within 60 degrees of the normal line: next
     // to a pad edge or corner a feature above one surface region can sit
     // behind the plane of a neighbouring one without being inside the pad
     if (!(fabs(sd) >= 0.5 * pt.d) || !(sd < below)) return;
-    ++cnt;
     sdmin = fmin(sdmin, sd);
   });
+  const bool any = group_mask(sdmin < INFINITY) != 0;
+  for (int q = PAIR_LANES / 2; q > 0; q >>= 1) sdmin = fmin(sdmin, __shfl_xor(sdmin, q, PAIR_LANES));
+  if (threadIdx.x % PAIR_LANES) return;
   if (mode == 1) {
-    if (cnt) atomicOr(&S->infeasible, 1);
+    if (any) atomicOr(&S->infeasible, 1);
     return;
   }
-  E.pflag[j] = cnt > 0;
-  if (cnt == 0) return;
+  E.pflag[j] = any;
+  if (!any) return;
   double* rec = E.prec + (size_t)PREC * j;
   for (int i = 0; i < 3; ++i) rec[i] = (sdmin - dsafe) * n[i];
   rec[3] = dsafe - sdmin;
@@ -1674,7 +1775,8 @@ __device__ __forceinline__ bool pair_edge_block(const EnvDesc& E, int k, double 
 }
 
 // Collision-free step bound of pad primitive j moving by alpha p (p the
-// direction at its vertices).  Per pair the larger of two safe bounds:
+// direction at its vertices), over this lane's pairs.  Per pair the larger of
+// two safe bounds:
 // conservative advancement (every point of the moving primitive moves at
 // most alpha max_a |p_a|, so the pair's distance d(alpha) is Lipschitz with
 // that constant, and from a reached alpha the step (d(alpha) - 0.1 d(0)) /
@@ -1685,7 +1787,7 @@ __device__ __forceinline__ bool pair_edge_block(const EnvDesc& E, int k, double 
 // does not count).  Pairs farther than FILTER_SPAN max |p_a| / 0.9 cannot
 // bind.
 template <typename R>
-__device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, const R* d, double span) {
+__device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, const R* d, double span, PairWork& W) {
   int vid[3];
   double xw[3][3], pv[3][3];
   const int nv = prim_load<R>(E, j, E.xn, nullptr, 0.0, vid, xw);
@@ -1699,10 +1801,9 @@ __device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, con
     pm = fmax(pm, sqrt(q));
   }
   if (!(pm > 0.0)) return INFINITY;
-  double r[MAX_IND];
-  for (int m = 0; m < MAX_IND; ++m) r[m] = span * pm / 0.9;
   double a = INFINITY;
-  visit_pairs(E, P, j, xw, r, [&](int m, const PairTerm& pt) {
+  visit_pairs(E, P, j, xw, W, [&](int) { return span * pm / 0.9; }, [&](int m, bool hit, const PairTerm& pt) {
+    if (!hit) return;
     const double floor_ = 0.1 * pt.d;
     if (!(pt.d > 0.0)) {
       a = 0.0;
@@ -3430,9 +3531,13 @@ hipError_t launch_typed(KernelId id, const LaunchArgs& a) {
       if (a.n_env > 0) TC_GO(k_env_extract, a.n_env, 256, a.stream, a.envs, a.n_env);
       break;
     case KernelId::commit: TC_LAUNCH(k_commit, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
-    case KernelId::pairs: TC_LAUNCH(k_pairs<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs, a.mode); break;
+    case KernelId::pairs:
+      if (a.mode == 3) TC_LAUNCH((k_pairs<R, true>), a.ntiles, PAIR_BLOCK, a.stream, a.tiles, a.ntiles, a.envs, a.mode);
+      else if (a.mode >= 2) TC_LAUNCH((k_pairs<R, false>), a.ntiles, PAIR_BLOCK, a.stream, a.tiles, a.ntiles, a.envs, a.mode);
+      else TC_LAUNCH(k_pair_records, a.ntiles, PAIR_BLOCK, a.stream, a.tiles, a.ntiles, a.envs, a.mode);
+      break;
     case KernelId::pair_push:
-      TC_LAUNCH(k_pair_push, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs, a.mode);
+      TC_LAUNCH(k_pair_push, a.ntiles, PAIR_BLOCK, a.stream, a.tiles, a.ntiles, a.envs, a.mode);
       break;
     case KernelId::pair_apply: TC_LAUNCH(k_pair_apply, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
     default: break;

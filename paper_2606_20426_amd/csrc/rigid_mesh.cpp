@@ -19,8 +19,6 @@ namespace tc {
 
 namespace {
 
-constexpr int kLeaf = 4;   // triangles per leaf
-
 using Vec3 = std::array<double, 3>;
 
 Vec3 sub(const Vec3& a, const Vec3& b) { return {a[0] - b[0], a[1] - b[1], a[2] - b[2]}; }
@@ -52,7 +50,7 @@ int build(Tree& t, int lo, int hi, const std::vector<Vec3>& cen, const std::vect
       chi[i] = std::max(chi[i], cen[f][i]);
     }
   }
-  if (hi - lo <= kLeaf) {
+  if (hi - lo <= MESH_LEAF) {
     nd.first = lo;
     nd.count = hi - lo;
     t.nodes[me] = nd;

@@ -67,6 +67,9 @@ constexpr int MAX_MESHES = 64;
 // below this (median splits, at most 2^24 triangles)
 constexpr int BVH_STACK = 64;
 
+// triangles per leaf of a hierarchy
+constexpr int MESH_LEAF = 4;
+
 // Bounding-volume hierarchy node, depth-first order (an inner node's left
 // child follows it).  count > 0: leaf over triangles [first, first + count);
 // count == 0: inner node whose right child is node `first`.
@@ -115,7 +118,13 @@ struct EnvPose {
 // each: 00 01 02 11 12 22) of vertex pairs (0,0) (1,1) (2,2) (0,1) (1,2)
 // (2,0).  During the feasible start the first four values hold the push
 // of the primitive's vertices and the number of pushes.
-constexpr int PREC = 48;
+constexpr int PAIR_VALUES = 45, PREC = 46;
+
+// Pair kernels: a group of PAIR_LANES lanes to a primitive, its nodes still to
+// be visited (beyond BVH_STACK of them one is taken at a time) and the leaf
+// slots found (emptied from PAIR_LANES on, at most a leaf a lane added at once).
+constexpr int PAIR_LANES = 16, PAIR_BLOCK = 256, PAIR_PRIMS = PAIR_BLOCK / PAIR_LANES;
+constexpr int PAIR_STACK = 128 + BVH_STACK, PAIR_SLOTS = PAIR_LANES * (MESH_LEAF + 1);
 
 // Lagged friction record of one (indenter, contact vertex) pair, float64:
 // normal force lambda (0 = no friction), normal n, indenter point motion w.
@@ -200,7 +209,7 @@ struct EnvDesc {
   int32_t Se;                // surface edges
   int32_t n_vt, n_tt, n_ct, n_st, n_at, n_te, n_spt;   // tiles per kernel class
   int32_t small;             // its CG runs in one block (k_cg_small)
-  int32_t n_pt;              // pair tiles over S + Se surface primitives (mesh_contact 2, else 0)
+  int32_t n_pt;              // pair tiles of PAIR_PRIMS over S + Se surface primitives (mesh_contact 2, else 0)
   // resident inputs
   TC_GLOBAL const double* X;
   TC_GLOBAL double* x;
