@@ -899,6 +899,12 @@ __device__ __forceinline__ int prim_verts(const EnvDesc& E, int j, int vid[3]) {
   return 2;
 }
 
+// World point x in indenter I's frame.
+__device__ __forceinline__ void mesh_local(const DevIndenter& I, const double x[3], double y[3]) {
+  for (int i = 0; i < 3; ++i)
+    y[i] = I.R[0 * 3 + i] * (x[0] - I.c[0]) + I.R[1 * 3 + i] * (x[1] - I.c[1]) + I.R[2 * 3 + i] * (x[2] - I.c[2]);
+}
+
 // Every pair of pad primitive j (vertices xw, world) with the mesh
 // indenters nearer than rad(m): fn(m, hit, PairTerm), called by the whole group
 // whenever one of its lanes hit a pair.
@@ -914,10 +920,7 @@ __device__ __forceinline__ void visit_pairs(const EnvDesc& E, const EnvPose* P, 
     if (I.shape != TC_MESH || !(r > 0.0)) continue;
     const DevMesh& M = E.meshes[I.reserved];
     double xl[3][3], lo[3], hi[3];
-    for (int k = 0; k < 3; ++k)
-      for (int i = 0; i < 3; ++i)
-        xl[k][i] = I.R[0 * 3 + i] * (xw[k][0] - I.c[0]) + I.R[1 * 3 + i] * (xw[k][1] - I.c[1]) +
-                   I.R[2 * 3 + i] * (xw[k][2] - I.c[2]);
+    for (int k = 0; k < 3; ++k) mesh_local(I, xw[k], xl[k]);
     for (int i = 0; i < 3; ++i) {
       lo[i] = fmin(fmin(xl[0][i], xl[1][i]), xl[2][i]) - r;
       hi[i] = fmax(fmax(xl[0][i], xl[1][i]), xl[2][i]) + r;
@@ -1003,6 +1006,76 @@ __device__ __forceinline__ void visit_pairs(const EnvDesc& E, const EnvPose* P, 
       }
     });
   }
+}
+
+// Barrier of one pad vertex (at x, world) against a rigid mesh summed over its
+// triangles nearer than d_hat, mesh_pair_world's terms, by a group.  Energy:
+// this lane's share of sum d_hat b(s_t).
+__device__ __forceinline__ double vertex_mesh_energy(const DevIndenter& I, const DevMesh* meshes, const double x[3],
+                                                     double dhat, PairWork& W) {
+  const DevMesh& M = meshes[I.reserved];
+  double y[3], lo[3], hi[3], e = 0.0;
+  mesh_local(I, x, y);
+  for (int i = 0; i < 3; ++i) { lo[i] = y[i] - dhat; hi[i] = y[i] + dhat; }
+  bvh_overlap(M, lo, hi, W, [&](int ns) {
+    for (int s = threadIdx.x & (PAIR_LANES - 1); s < ns; s += PAIR_LANES) {
+      double c[3];
+      tri_closest(M.tv + 9 * (size_t)W.slots[s], y, c);
+      const double df[3] = {y[0] - c[0], y[1] - c[1], y[2] - c[2]};
+      const double d2 = df[0] * df[0] + df[1] * df[1] + df[2] * df[2];
+      if (d2 < dhat * dhat) e += dhat * bar0(sqrt(d2) / dhat);
+    }
+  });
+  return e;
+}
+
+// Gradient and Hessian (with curv 0 its normal part alone), summed over the
+// group and added to g and H (xx xy xz yy yz zz) with weight kA.
+__device__ __forceinline__ void vertex_mesh_terms(const DevIndenter& I, const DevMesh* meshes, const double x[3],
+                                                  double dhat, bool curv, double kA, PairWork& W, double g[3],
+                                                  double H[6]) {
+  const DevMesh& M = meshes[I.reserved];
+  double y[3], lo[3], hi[3], gl[3] = {0, 0, 0}, Hl[6] = {0, 0, 0, 0, 0, 0};
+  mesh_local(I, x, y);
+  for (int i = 0; i < 3; ++i) { lo[i] = y[i] - dhat; hi[i] = y[i] + dhat; }
+  bvh_overlap(M, lo, hi, W, [&](int ns) {
+    for (int s = threadIdx.x & (PAIR_LANES - 1); s < ns; s += PAIR_LANES) {
+      double c[3];
+      const double* T = M.tv + 9 * (size_t)W.slots[s];
+      const int r = tri_closest(T, y, c);
+      const double df[3] = {y[0] - c[0], y[1] - c[1], y[2] - c[2]};
+      const double d2 = df[0] * df[0] + df[1] * df[1] + df[2] * df[2];
+      if (!(d2 < dhat * dhat) || !(d2 > 0.0)) continue;
+      const double d = sqrt(d2), sd = d / dhat;
+      const double b1 = bar1(sd), b2 = bar2(sd) / dhat;
+      const double gd[3] = {df[0] / d, df[1] / d, df[2] / d};
+      double tv[3] = {0, 0, 0};
+      if (r >= 4) {
+        const int e0 = r - 4, e1 = (r - 4 + 1) % 3;
+        for (int i = 0; i < 3; ++i) tv[i] = T[3 * e1 + i] - T[3 * e0 + i];
+        const double L = sqrt(tv[0] * tv[0] + tv[1] * tv[1] + tv[2] * tv[2]);
+        for (int i = 0; i < 3; ++i) tv[i] /= L;
+      }
+      const double cv = curv && r ? b1 / d : 0.0;
+      for (int i = 0, q = 0; i < 3; ++i) {
+        gl[i] += b1 * gd[i];
+        for (int j = i; j < 3; ++j, ++q)
+          Hl[q] += b2 * gd[i] * gd[j] + cv * ((i == j ? 1.0 : 0.0) - tv[i] * tv[j] - gd[i] * gd[j]);
+      }
+    }
+  });
+  for (int i = 0; i < 3; ++i) gl[i] = row_sum16(gl[i]);
+  for (int q = 0; q < 6; ++q) Hl[q] = row_sum16(Hl[q]);
+  const double A[3][3] = {{Hl[0], Hl[1], Hl[2]}, {Hl[1], Hl[3], Hl[4]}, {Hl[2], Hl[4], Hl[5]}};
+  double T[3][3];
+  for (int i = 0; i < 3; ++i) {
+    g[i] += kA * (I.R[i * 3 + 0] * gl[0] + I.R[i * 3 + 1] * gl[1] + I.R[i * 3 + 2] * gl[2]);
+    for (int j = 0; j < 3; ++j)
+      T[i][j] = I.R[i * 3 + 0] * A[0][j] + I.R[i * 3 + 1] * A[1][j] + I.R[i * 3 + 2] * A[2][j];
+  }
+  for (int i = 0, q = 0; i < 3; ++i)
+    for (int j = i; j < 3; ++j, ++q)
+      H[q] += kA * (T[i][0] * I.R[j * 3 + 0] + T[i][1] * I.R[j * 3 + 1] + T[i][2] * I.R[j * 3 + 2]);
 }
 
 // Loads pad primitive j's vertex positions x (+ al * d when d is given; an
@@ -1497,8 +1570,20 @@ __device__ __forceinline__ bool extract_ok(const EnvState* S);
 template <typename R>
 __device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, const R* d, double span, PairWork& W);
 
-// Per surface primitive (pad triangles, then surface edges) of pads with
-// vertex-face / edge-edge pairs, a group of lanes each:
+// Whether the filter of the barrier Hessian takes its normal part alone, and
+// the filter's mode: 0 clamp, 1 as is, 2 normal term only, 3 clamp until a full
+// Newton step is accepted, then as is.
+__device__ __forceinline__ int barrier_filter(const EnvDesc& E) {
+  int mode = (E.hess_proj >> 2) & 3;
+  if (mode == 3) mode = E.st->true_hess ? 1 : 0;
+  return E.st->filt_all ? 0 : mode;   // (a CG breakdown earlier in this step)
+}
+
+// Per surface primitive (pad triangles, then surface edges, then contact
+// vertices) of pads with vertex-face / edge-edge pairs, a group of lanes each;
+// the contact vertices take part in all modes but 3, with their own terms
+// against the mesh indenters (gradient and Hessian go to gb and Hb, from which
+// the barrier and contact kernels go on):
 //   mode 0: records at the Newton iterate (pads running), mode 1: at the
 //           extraction positions: gradient and Gauss-Newton blocks of the
 //           primitive's pairs within d_hat, flag 0 for a primitive without
@@ -1513,7 +1598,11 @@ __device__ double prim_pair_bound(const EnvDesc& E, const EnvPose* P, int j, con
 // pairs pass through LDS, have a kernel of their own, and the step bound
 // (BOUND) one of more registers.  What bounds them is the chain of loads from
 // a primitive through its hierarchy to its pairs: 16 primitives to a block
-// give most groups one primitive of work and every CU several blocks.
+// give most groups one primitive of work and every CU several blocks.  8 pads
+// of 14k primitives and 4k contact vertices, against one thread each: energy
+// 121 -> 16 us, records 347 -> 35 us, pushes 146 -> 36 us; the contact
+// vertices' share out of the barrier kernel 107 -> 12 us, out of the line
+// search's energy launches 37 -> 6 us.
 template <typename R, bool BOUND>
 __global__ void __launch_bounds__(PAIR_BLOCK, BOUND ? 2 : 4) k_pairs(const Tile* tiles, int ntiles, const EnvDesc* envs, int mode) {
   __shared__ double sh[16];
@@ -1528,20 +1617,29 @@ __global__ void __launch_bounds__(PAIR_BLOCK, BOUND ? 2 : 4) k_pairs(const Tile*
   if (mode == 2 ? !searching(S) : mode == 4 ? !initialising(S) : !dir_ready(S)) return;
   // block reductions: every thread of the block takes part
   const int grp = threadIdx.x / PAIR_LANES, j = tl.tile * PAIR_PRIMS + grp;
-  const bool in = j < E.S + E.Se;
+  const int prims = E.S + E.Se;
   if (BOUND) {
     double a = INFINITY;
-    if (in) a = fmin(prim_pair_bound<R>(E, P, j, (const R*)E.d, FILTER_SPAN, work[grp]), FILTER_SPAN);
+    if (j < prims) a = fmin(prim_pair_bound<R>(E, P, j, (const R*)E.d, FILTER_SPAN, work[grp]), FILTER_SPAN);
     a = block_reduce(a, OpMin(), sh);
     if (threadIdx.x == 0) E.part_filt[E.n_ct + tl.tile] = a;
     return;
   }
   double e = 0.0;
-  if (in) {
+  const R* d = mode == 2 ? (const R*)E.d : nullptr;
+  const double al = mode == 2 ? S->ls_alpha : 0.0;
+  if (j < prims) {
     int vid[3];
     double xw[3][3];
-    prim_load<R>(E, j, E.xn, mode == 2 ? (const R*)E.d : nullptr, mode == 2 ? S->ls_alpha : 0.0, vid, xw);
+    prim_load<R>(E, j, E.xn, d, al, vid, xw);
     e = prim_pair_energy(E, P, j, xw, work[grp]);
+  } else if (j - prims < E.C) {
+    const int vi = E.cand[j - prims];
+    double y[3];
+    for (int c = 0; c < 3; ++c) y[c] = E.xn[3 * vi + c] + (d ? al * (double)d[3 * vi + c] : 0.0);
+    const double kA = E.kappa * E.cand_area[j - prims];
+    for (int m = 0; m < P->n_ind; ++m)
+      if (P->ind[m].shape == TC_MESH) e += kA * vertex_mesh_energy(P->ind[m], E.meshes, y, E.dhat, work[grp]);
   }
   e = block_reduce(e, OpSum(), sh);
   if (threadIdx.x == 0) E.part_e[E.n_te + E.n_vt + E.n_ct + tl.tile] = e;
@@ -1564,10 +1662,26 @@ __global__ void __launch_bounds__(PAIR_BLOCK) k_pair_records(const Tile* tiles, 
   if (!pair_active(E, P)) return;
   if (mode == 0 ? !at_stage(S, ST_ASM) : !extract_ok(S)) return;
   const int grp = threadIdx.x / PAIR_LANES, lane = threadIdx.x % PAIR_LANES, j = tl.tile * PAIR_PRIMS + grp;
-  if (j >= E.S + E.Se) return;
+  const double* x = (mode == 1 && S->mode == 1) ? E.x : E.xn;
+  const int prims = E.S + E.Se;
+  if (j >= prims) {
+    const int k = j - prims;
+    if (k >= E.C) return;
+    double xv[3], g[3] = {0, 0, 0}, H[6] = {0, 0, 0, 0, 0, 0};
+    load3(x, E.cand[k], xv);
+    for (int m = 0; m < P->n_ind; ++m)
+      if (P->ind[m].shape == TC_MESH)
+        vertex_mesh_terms(P->ind[m], E.meshes, xv, E.dhat, barrier_filter(E) != 2, E.kappa * E.cand_area[k],
+                          work[grp], g, H);
+    if (lane == 0) {
+      for (int i = 0; i < 3; ++i) E.gb[3 * k + i] = g[i];
+      for (int q = 0; q < 6; ++q) E.Hb[6 * k + q] = H[q];
+    }
+    return;
+  }
   int vid[3];
   double xw[3][3];
-  prim_load<double>(E, j, (mode == 1 && S->mode == 1) ? E.x : E.xn, nullptr, 0.0, vid, xw);
+  prim_load<double>(E, j, x, nullptr, 0.0, vid, xw);
   // lane's values of the record: lane, lane + 16 and lane + 32 of the 9 of the
   // gradient and the 6 x 6 of the blocks (0,0) (1,1) (2,2) (0,1) (1,2) (2,0)
   constexpr int N = (PAIR_VALUES + PAIR_LANES - 1) / PAIR_LANES;
@@ -1871,8 +1985,16 @@ __global__ void k_barrier(const Tile* tiles, int ntiles, const EnvDesc* envs) {
   load3(E.xn, vi, x);
   const double kA = E.kappa * E.cand_area[k];
   double g[3] = {0, 0, 0}, H[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Hn[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+  const bool pairs = pair_active(E, P);
+  if (pairs) {                          // the mesh indenters' terms come from the pair records
+    load3(E.gb, k, g);
+    const double* hb = E.Hb + 6 * k;
+    for (int i = 0, q = 0; i < 3; ++i)
+      for (int j = i; j < 3; ++j, ++q) H[i][j] = H[j][i] = Hn[i][j] = Hn[j][i] = hb[q];
+  }
   for (int m = 0; m < P->n_ind; ++m) {
     if (E.mesh_pairs && P->ind[m].shape == TC_MESH) {
+      if (pairs) continue;
       double e, gp[3], Hq[3][3], Hnq[3][3];
       mesh_pair_world(P->ind[m], E.meshes, x, E.dhat, true, e, gp, Hq, Hnq);
       for (int i = 0; i < 3; ++i) {
@@ -1898,11 +2020,7 @@ __global__ void k_barrier(const Tile* tiles, int ntiles, const EnvDesc* envs) {
       }
     }
   }
-  // 0 clamp, 1 as is, 2 normal term only, 3 clamp until a full Newton step
-  // is accepted, then as is
-  int bmode = (E.hess_proj >> 2) & 3;
-  if (bmode == 3) bmode = E.st->true_hess ? 1 : 0;
-  if (E.st->filt_all) bmode = 0;   // a CG breakdown earlier in this step
+  const int bmode = barrier_filter(E);
   if (bmode == 0) {
     project_psd3(H);
   } else if (bmode == 2) {
@@ -1911,7 +2029,7 @@ __global__ void k_barrier(const Tile* tiles, int ntiles, const EnvDesc* envs) {
   }
   // vertex-face and edge-edge pairs of the vertex's surface primitives
   // (Gauss-Newton, PSD: added after the filter)
-  if (pair_active(E, P)) pair_gather(E, k, g, H);
+  if (pairs) pair_gather(E, k, g, H);
   // lagged friction (PSD by construction, added after the filter):
   // gradient mu lambda (f1/y) u, Hessian mu lambda [f1/y (P - uh uh^T) +
   // f1' uh uh^T] with P = I - n n^T and uh = u / |u| (u lies in P's range)
@@ -3062,6 +3180,7 @@ __global__ void k_energy(const Tile* tiles, int ntiles, const EnvDesc* envs, int
       for (int m = 0; m < P->n_ind; ++m) {
         double phi;
         if (E.mesh_pairs && P->ind[m].shape == TC_MESH) {
+          if (pair_active(E, P)) continue;    // (k_pairs has these)
           double Hn[3][3];
           mesh_pair_world(P->ind[m], E.meshes, y, E.dhat, false, phi, g, H, Hn);
           acc += E.kappa * E.cand_area[k] * phi;
@@ -3353,9 +3472,13 @@ __global__ void k_contact(const Tile* tiles, int ntiles, const EnvDesc* envs) {
     load3(x, vi, xv);
     const double kA = E.kappa * E.cand_area[k];
     double f[3] = {0, 0, 0};
+    const bool pairs = pair_active(E, P);
+    if (pairs)                          // the mesh indenters' terms come from the pair records
+      for (int c = 0; c < 3; ++c) f[c] = -E.gb[3 * k + c];
     for (int m = 0; m < P->n_ind; ++m) {
       double phi, g[3];
       if (E.mesh_pairs && P->ind[m].shape == TC_MESH) {
+        if (pairs) continue;
         double Hn[3][3];
         mesh_pair_world(P->ind[m], E.meshes, xv, E.dhat, false, phi, g, H, Hn);
         for (int c = 0; c < 3; ++c) f[c] -= kA * g[c];
@@ -3368,7 +3491,7 @@ __global__ void k_contact(const Tile* tiles, int ntiles, const EnvDesc* envs) {
       }
     }
     // vertex-face and edge-edge pairs of the vertex's surface primitives
-    if (pair_active(E, P)) {
+    if (pairs) {
       double gp[3] = {0, 0, 0};
       pair_gather(E, k, gp, nullptr);
       for (int c = 0; c < 3; ++c) f[c] -= gp[c];

@@ -372,7 +372,7 @@ static ScratchLayout scratch_layout(const tc_pad* p) {
   L.Hb = take(48 * C);
   L.fric = take(p->params.friction > 0 ? 8 * FRIC_STRIDE * MAX_IND * C : 0);
   const size_t nv = cdiv(V, 64), nt = cdiv(T, 64), nc = cdiv(C, 64), ns = cdiv(std::max<size_t>(S, 1), 64);
-  const size_t NP = pair_prims(p), np = cdiv(NP, PAIR_PRIMS);
+  const size_t NP = pair_prims(p), np = NP ? cdiv(NP + C, PAIR_PRIMS) : 0;
   L.prz = take(8 * nv);
   L.ppq = take(8 * ((size_t)cdiv(V, 2) + 1));
   L.pg2 = take(8 * nv);
@@ -564,7 +564,7 @@ tc_status build_plan(tc_context* ctx, int n, tc_pad* const* pads, const int* slo
     E.n_at = cdiv((int64_t)E.V_E, BV);
     E.n_te = cdiv(p->T, BV);
     E.n_spt = cdiv(p->V, rows_spmv);
-    E.n_pt = E.prec ? cdiv((int64_t)p->S + p->Se, PAIR_PRIMS) : 0;
+    E.n_pt = E.prec ? cdiv((int64_t)p->S + p->Se + p->C, PAIR_PRIMS) : 0;
     // (its sums are those of launched blocks of 256)
     E.small = P->lpr == 16 && BV == 256 && ctx->spmv_block == 256 && cg_small_rows(p->V, p->W, p->fp64);
     E.st = pool.d_state + slots[i];

@@ -209,7 +209,7 @@ struct EnvDesc {
   int32_t Se;                // surface edges
   int32_t n_vt, n_tt, n_ct, n_st, n_at, n_te, n_spt;   // tiles per kernel class
   int32_t small;             // its CG runs in one block (k_cg_small)
-  int32_t n_pt;              // pair tiles of PAIR_PRIMS over S + Se surface primitives (mesh_contact 2, else 0)
+  int32_t n_pt;              // pair tiles of PAIR_PRIMS over S + Se surface primitives and C contact vertices (mesh_contact 2, else 0)
   // resident inputs
   TC_GLOBAL const double* X;
   TC_GLOBAL double* x;
