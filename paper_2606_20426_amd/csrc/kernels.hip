@@ -1599,8 +1599,8 @@ __device__ __forceinline__ int barrier_filter(const EnvDesc& E) {
 // (BOUND) one of more registers.  What bounds them is the chain of loads from
 // a primitive through its hierarchy to its pairs: 16 primitives to a block
 // give most groups one primitive of work and every CU several blocks.  8 pads
-// of 14k primitives and 4k contact vertices, against one thread each: energy
-// 121 -> 16 us, records 347 -> 35 us, pushes 146 -> 36 us; the contact
+// with 14k primitives in all and their contact vertices, one thread each ->
+// these: energy 121 -> 16 us, records 347 -> 35 us, pushes 146 -> 36 us; the
 // vertices' share out of the barrier kernel 107 -> 12 us, out of the line
 // search's energy launches 37 -> 6 us.
 template <typename R, bool BOUND>
@@ -2269,22 +2269,61 @@ __global__ void k_asm_diag(const Tile* tiles, int ntiles, const EnvDesc* envs) {
 // Off-diagonal blocks, one thread per unique edge i < j: sum of the edge
 // blocks of every tet sharing it, times h^2, written to (i, slot of j) and
 // transposed to (j, slot of i), Dirichlet rows and columns zeroed.
+//
+// A wave's 64 edges own one contiguous run of records, which it copies to LDS
+// in 16-byte loads; each thread sums its edge's from there, in order, and the
+// results leave through LDS too, 9 lanes to a block.  Read and written by the
+// threads themselves, 36 bytes apart or at random, nearly every lane is a
+// request of its own to L2, and these, not the bytes, set the time.  1.2M tets
+// (1.5M edges, 0.37 GB), mixed: 158 -> 95 us; 60 pads of 3M in all, in halves: 68
+// -> 52; 12 pads of 0.4M in all, double: 19 -> 15.
+constexpr int ASM_BYTES = 9216;         // records in LDS per wave at a time
+
 template <typename R>
-__global__ void k_asm_off(const Tile* tiles, int ntiles, const EnvDesc* envs) {
+__global__ void __launch_bounds__(ASM_BLOCK) k_asm_off(const Tile* tiles, int ntiles, const EnvDesc* envs) {
+  constexpr int VEC = 16 / sizeof(R), WORDS = ASM_BYTES / sizeof(R), NR = (WORDS - VEC + 1) / KC;
+  using Vec = R __attribute__((ext_vector_type(VEC)));
+  __shared__ Vec buf[ASM_BLOCK / 64][WORDS / VEC];
+  __shared__ int2 pos[ASM_BLOCK / 64][64];
   const int t = xcd_tile(ntiles);
   if (t < 0) return;
   const EnvDesc& E = envs[tiles[t].env];
   if (!at_stage(E.st, ST_ASM)) return;
-  const int k = tiles[t].tile * blockDim.x + threadIdx.x;
-  if (k >= E.V_E) return;
-  const R* Ko = (const R*)E.Ke + (size_t)KC * 4 * E.T;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int k0 = tiles[t].tile * ASM_BLOCK + 64 * wave, k = min(k0 + lane, E.V_E - 1);
+  if (k0 >= E.V_E) return;              // (the wave's LDS is its own: no barriers)
+  const bool in = k0 + lane < E.V_E;
+  const int last = E.eptr[k + 1], first = in ? E.eptr[k] : last;
+  const int2 it = reinterpret_cast<const int2*>(E.eitem)[k];
+  const uint8_t fi = E.fixed[it.x / E.W], fj = E.fixed[it.y / E.W];
+  pos[wave][lane] = in ? it : make_int2(-1, -1);
+  const int begin = __builtin_amdgcn_readfirstlane(first), end = __builtin_amdgcn_readlane(last, 63);
+  const R* Ko = (const R*)E.Ke + (size_t)KC * 4 * E.T;     // (a multiple of 16 bytes into Ke)
+  const R* lds = (const R*)buf[wave];
   R acc[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  for (int c = E.eptr[k]; c < E.eptr[k + 1]; ++c) {
-    const R* p = Ko + (size_t)KC * c;
+  for (int c0 = begin; c0 < end; c0 += NR) {
+    const int c1 = min(c0 + NR, end);
+    // whole vectors around the records; the last may run past the stream into
+    // the padding that follows it
+    const size_t w = (size_t)KC * c0, w0 = w & ~(size_t)(VEC - 1);
+    const int skip = (int)(w - w0), n = (skip + KC * (c1 - c0) + VEC - 1) / VEC;
+    const Vec* src = (const Vec*)(Ko + w0);
+    Vec v[9];
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 9; ++q)
+      if (64 * q < n) v[q] = src[min(64 * q + lane, n - 1)];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) acc[r][q] += p[3 * r + q];
+    for (int q = 0; q < 9; ++q)
+      if (64 * q < n) buf[wave][64 * q + lane] = v[q];
+    wave_sync();
+    for (int c = max(first, c0); c < min(last, c1); ++c) {
+      const R* p = lds + skip + KC * (c - c0);
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) acc[r][q] += p[3 * r + q];
+    }
+    wave_sync();
   }
   // pair Gauss-Newton block of a surface edge (mesh_contact 2)
   double pb[6];
@@ -2295,19 +2334,23 @@ __global__ void k_asm_off(const Tile* tiles, int ntiles, const EnvDesc* envs) {
 #pragma unroll
       for (int q = 0; q < 3; ++q) acc[r][q] = (R)((double)acc[r][q] + B[r][q]);
   }
-  const int2 it = reinterpret_cast<const int2*>(E.eitem)[k];
-  const int i = it.x / E.W, j = it.y / E.W;
   const R h2 = (R)(E.h * E.h);
-  const uint8_t fi = E.fixed[i], fj = E.fixed[j];
-  R* Aij = (R*)E.A + (size_t)it.x * 9;
-  R* Aji = (R*)E.A + (size_t)it.y * 9;
+  R* out = (R*)buf[wave] + KC * lane;
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      Aij[3 * r + q] = (((fi >> r) & 1) || ((fj >> q) & 1)) ? R(0) : acc[r][q] * h2;
-      Aji[3 * q + r] = (((fj >> q) & 1) || ((fi >> r) & 1)) ? R(0) : acc[r][q] * h2;
+    for (int q = 0; q < 3; ++q) out[3 * r + q] = (((fi >> r) & 1) || ((fj >> q) & 1)) ? R(0) : acc[r][q] * h2;
+  wave_sync();
+  R* A = (R*)E.A;
+#pragma unroll
+  for (int q = 0; q < KC; ++q) {
+    const int f = 64 * q + lane, e = f / KC, m = f % KC;
+    const int2 to = pos[wave][e];
+    if (to.x >= 0) {
+      A[(size_t)to.x * KC + m] = lds[f];
+      A[(size_t)to.y * KC + m] = lds[KC * e + 3 * (m % 3) + m / 3];
     }
+  }
 }
 
 // ------------------------------------------------------ CG (a5)
@@ -3612,7 +3655,7 @@ hipError_t launch_typed(KernelId id, const LaunchArgs& a) {
     case KernelId::element: TC_LAUNCH(k_element<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
     case KernelId::barrier: TC_LAUNCH(k_barrier, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
     case KernelId::asm_diag: TC_LAUNCH(k_asm_diag<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
-    case KernelId::asm_off: TC_LAUNCH(k_asm_off<R>, a.ntiles, a.block, a.stream, a.tiles, a.ntiles, a.envs); break;
+    case KernelId::asm_off: TC_LAUNCH(k_asm_off<R>, a.ntiles, ASM_BLOCK, a.stream, a.tiles, a.ntiles, a.envs); break;
     case KernelId::newton_begin:
       if (a.n_env > 0) TC_GO(k_env_newton_begin, a.n_env, 64, a.stream, a.envs, a.n_env);
       break;

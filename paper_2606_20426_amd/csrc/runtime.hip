@@ -561,7 +561,7 @@ tc_status build_plan(tc_context* ctx, int n, tc_pad* const* pads, const int* slo
     E.n_tt = cdiv(p->T, BT);
     E.n_ct = p->C > 0 ? cdiv(p->C, BV) : 0;
     E.n_st = cdiv(p->S, BV);
-    E.n_at = cdiv((int64_t)E.V_E, BV);
+    E.n_at = cdiv((int64_t)E.V_E, ASM_BLOCK);
     E.n_te = cdiv(p->T, BV);
     E.n_spt = cdiv(p->V, rows_spmv);
     E.n_pt = E.prec ? cdiv((int64_t)p->S + p->Se + p->C, PAIR_PRIMS) : 0;

@@ -44,6 +44,9 @@ __host__ __device__ constexpr bool cg_small_rows(int V, int W, bool fp64) {
   return W <= 16 && V <= (fp64 ? 640 : CG_SMALL);
 }
 
+// edges per tile of the off-diagonal assembly
+constexpr int ASM_BLOCK = 256;
+
 // offset of block (a, b), a <= b, inside the record; diagonal blocks hold
 // (xx, xy, xz, yy, yz, zz), off-diagonal blocks row-major 3x3
 __host__ __device__ constexpr int ke_block_offset(int a, int b) {

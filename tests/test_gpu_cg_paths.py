@@ -96,6 +96,21 @@ def test_small_pads_in_a_mixed_batch_keep_their_bits(prec, warm):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
+@pytest.mark.parametrize("sectors", [40, 300])
+def test_long_runs_of_edge_records(sectors):
+    """The axis edges of a fan are shared by every sector's tets: runs of
+    records below and beyond the 127 that a wave holds at a time in float64."""
+    X, T = meshes.fan_prisms(sectors, 6 * MM, 3 * MM, 2)
+    pad = scenes.Pad("fan", X, T, scenes.Material(), (12 * MM, 12 * MM, 3 * MM))
+    ind = scenes.place_indenter(pad, scenes.SPHERE, (0.0, 0.0), 1e-4, sphere_radius=4 * MM).at_depth(0.06 * MM)
+    ref = _exact(pad, ind, stepper.StepParams(newton_tol=1e-10, quasi_static=True))
+    ctx = tc.Context(0)
+    gp = gpu_pad(ctx, pad, "fp64", quasi_static=1, cg_rel_tol=1e-12, cg_forcing=0)
+    d, _ = gp.newton_direction([ind])
+    ctx.close()
+    assert np.abs(d - ref).max() / np.abs(ref).max() < 1e-7
+
+
 def test_partial_sums_shared_over_the_block():
     """More than 512 partials of a dot product are summed by the whole block:
     on 17k rows, products of 64-thread blocks leave 1,077 partials, those of
