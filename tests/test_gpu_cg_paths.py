@@ -114,14 +114,16 @@ def test_long_runs_of_edge_records(sectors):
 def test_partial_sums_shared_over_the_block():
     """More than 512 partials of a dot product are summed by the whole block:
     on 17k rows, products of 64-thread blocks leave 1,077 partials, those of
-    256-thread blocks 270.  Both solve to 1e-10; the directions differ by what
-    the solver leaves, far below 1e-6."""
+    256-thread blocks 270; a vector kernel of 256 threads takes the 1,077 in one
+    round of loads, one of 64 in three.  All solve to 1e-10; the directions
+    differ by what the solver leaves, far below 1e-6."""
     pad, ind = _pressed((40, 34, 11))
-    d = {}
-    for block in (256, 64):
+    d = []
+    for cg_block, spmv_block in ((256, 256), (256, 64), (64, 64)):
         ctx = tc.Context(0)
-        ctx.set_launch(cg_block=block, spmv_block=block)
+        ctx.set_launch(cg_block=cg_block, spmv_block=spmv_block)
         gp = gpu_pad(ctx, pad, "fp64", quasi_static=1, cg_rel_tol=1e-10, cg_forcing=0)
-        d[block], _ = gp.newton_direction([ind])
+        d.append(gp.newton_direction([ind])[0])
         ctx.close()
-    assert np.abs(d[256] - d[64]).max() < 1e-6 * np.abs(d[256]).max()
+    for other in d[1:]:
+        assert np.abs(d[0] - other).max() < 1e-6 * np.abs(d[0]).max()
