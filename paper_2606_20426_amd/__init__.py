@@ -267,6 +267,7 @@ class Pad:
                  fixed=None, tet_material=None):
         self.ctx = ctx
         self.lib = ctx.lib
+        self._layouts = {}
         mats = materials if isinstance(materials, (list, tuple)) else [materials]
         marr = (_abi.TcMaterial * len(mats))()
         for i, m in enumerate(mats):
@@ -340,7 +341,10 @@ class Pad:
 
     def read(self, field, device: bool = False):
         """numpy array (host) or torch tensor on the context's device."""
-        f, dt, n, c = self.field_info(field)
+        layout = self._layouts.get(field)
+        if layout is None:      # a field's layout never changes
+            layout = self._layouts[field] = self.field_info(field)
+        f, dt, n, c = layout
         shape = (n, c) if c > 1 else (n,)
         if device:
             import torch

@@ -4,6 +4,7 @@
 // state, indenter poses, tile lists and partial sums live in one file-scope
 // device array of fixed size instead of the context's step scratch, plan and
 // state pool; the kernels are the ones tc_extract launches.
+#include <cstring>
 #include <mutex>
 
 #include "runtime.h"
@@ -25,10 +26,31 @@ void* g_ptr[MAX_DEVICES] = {};
 size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Tile list {pad 0, tile i} for i < n.
-__global__ void k_noalloc_tiles(Tile* t, int n) {
+// Everything the call's kernels read, passed by value: the descriptor, state
+// and poses go to the scratch array, and the three tile lists {pad 0, tile i} of
+// n[c] tiles are written behind one another.  One launch (2.3 us of the host)
+// instead of three copies from unpinned memory (4 us each) and three fills.
+struct NoallocArgs {
+  EnvDesc desc;
+  EnvState state;
+  EnvPose pose;
+  int n[3];
+};
+static_assert(sizeof(NoallocArgs) <= 4000 && sizeof(EnvDesc) % 4 == 0 && sizeof(EnvState) % 4 == 0 &&
+              sizeof(EnvPose) % 4 == 0, "kernel argument limit");
+
+__global__ void k_noalloc_setup(NoallocArgs a, uint32_t* desc, uint32_t* state, uint32_t* pose, Tile* tiles) {
+  if (blockIdx.x == 0) {
+    auto put = [](uint32_t* to, const void* from, int words) {
+      for (int i = threadIdx.x; i < words; i += blockDim.x) to[i] = static_cast<const uint32_t*>(from)[i];
+    };
+    put(desc, &a.desc, sizeof a.desc / 4);
+    put(state, &a.state, sizeof a.state / 4);
+    put(pose, &a.pose, sizeof a.pose / 4);
+  }
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) t[i] = Tile{0, i};
+  if (i < a.n[0] + a.n[1] + a.n[2])
+    tiles[i] = Tile{0, i < a.n[0] ? i : i < a.n[0] + a.n[1] ? i - a.n[0] : i - a.n[0] - a.n[1]};
 }
 
 }  // namespace
@@ -83,7 +105,9 @@ tc_status tc_extract_noalloc(tc_pad* pad, int32_t n_ind, const tc_indenter* ind,
   if (off > NOALLOC_BYTES)
     return set_error(TC_E_INVALID_ARG, "pad needs " + std::to_string(off) + " bytes of no-alloc scratch, more than " +
                                            std::to_string(NOALLOC_BYTES));
-  EnvDesc E = pad->desc;
+  NoallocArgs args;
+  EnvDesc& E = args.desc;
+  E = pad->desc;
   E.n_tt = n_tt;
   E.n_st = n_st;
   E.n_ct = n_ct;
@@ -91,25 +115,23 @@ tc_status tc_extract_noalloc(tc_pad* pad, int32_t n_ind, const tc_indenter* ind,
   E.part_s3 = reinterpret_cast<double*>(base + o_s3);
   E.st = reinterpret_cast<EnvState*>(base + o_state);
   E.pose = reinterpret_cast<const EnvPose*>(base + o_pose);
-  EnvState S;
-  EnvPose Q;
-  init_state(S, Q, 1, n_ind, ind, pad);
+  EnvPose& Q = args.pose;
+  init_state(args.state, Q, 1, n_ind, ind, pad);
   if (Q.pairs)
     return set_error(TC_E_INVALID_ARG,
                      "vertex-face / edge-edge pairs (mesh_contact 2 with a mesh indenter) need the pad's step "
                      "scratch: use tc_extract");
   hipStream_t st = ctx->stream;
-  TC_HIP(hipMemcpyAsync(base + o_desc, &E, sizeof E, hipMemcpyHostToDevice, st));
-  TC_HIP(hipMemcpyAsync(base + o_state, &S, sizeof S, hipMemcpyHostToDevice, st));
-  TC_HIP(hipMemcpyAsync(base + o_pose, &Q, sizeof Q, hipMemcpyHostToDevice, st));
   Tile* tiles = reinterpret_cast<Tile*>(base + o_tiles);
   Tile* t_tet = tiles;
   Tile* t_surf = tiles + n_tt;
   Tile* t_cand = tiles + n_tt + n_st;
-  const int counts[3] = {n_tt, n_st, n_ct};
-  Tile* lists[3] = {t_tet, t_surf, t_cand};
-  for (int c = 0; c < 3; ++c)
-    if (counts[c] > 0) hipLaunchKernelGGL(k_noalloc_tiles, dim3(cdiv(counts[c], 256)), dim3(256), 0, st, lists[c], counts[c]);
+  args.n[0] = n_tt;
+  args.n[1] = n_st;
+  args.n[2] = n_ct;
+  hipLaunchKernelGGL(k_noalloc_setup, dim3(cdiv((int64_t)n_tt + n_st + n_ct, 256)), dim3(256), 0, st, args,
+                     reinterpret_cast<uint32_t*>(base + o_desc), reinterpret_cast<uint32_t*>(base + o_state),
+                     reinterpret_cast<uint32_t*>(base + o_pose), tiles);
   const EnvDesc* d_desc = reinterpret_cast<const EnvDesc*>(base + o_desc);
   auto go = [&](KernelId k, const Tile* t, int nt, int block) {
     LaunchArgs a;
@@ -126,8 +148,9 @@ tc_status tc_extract_noalloc(tc_pad* pad, int32_t n_ind, const tc_indenter* ind,
   (void)go(KernelId::contact, t_cand, n_ct, ctx->cg_block);
   (void)go(KernelId::env_extract, nullptr, 0, 256);
   TC_HIP(hipGetLastError());
-  TC_HIP(hipMemcpyAsync(&S, base + o_state, sizeof S, hipMemcpyDeviceToHost, st));
-  TC_HIP(hipStreamSynchronize(st));
+  if ((s = ctx->sig.publish(base + o_state, ctx->sig.buf(), sizeof(EnvState), st))) return s;
+  EnvState S;
+  std::memcpy(&S, ctx->sig.buf(), sizeof S);
   if (S.status != TC_OK) return set_error(S.status, "extraction failed");
   if (reaction)
     for (int c = 0; c < 3; ++c) reaction[c] = S.reaction[c];

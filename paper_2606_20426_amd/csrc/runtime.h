@@ -71,8 +71,24 @@ struct TimingSlice {
 
 // Device array of per-step states and poses with pinned host mirrors; a pad
 // in a batch occupies one slot.
+// A pinned word (and PUBLISH_BYTES of pinned memory after it) in which a stream
+// reports: publish() copies up to PUBLISH_BYTES there, or to other pinned
+// memory, and returns once everything on the stream is done.  One waiting
+// thread at a time.
+constexpr size_t PUBLISH_BYTES = 32768;
+struct Signal {
+  uint64_t* flag = nullptr;
+  uint64_t seq = 0;
+  void* buf() const { return flag + 8; }
+  tc_status init();
+  void free();
+  tc_status publish(const void* src, void* dst, size_t bytes, hipStream_t stream);   // (multiples of 8)
+  tc_status wait(hipStream_t stream) { return publish(nullptr, nullptr, 0, stream); }
+};
+
 struct SlotPool {
   int cap = 0;
+  Signal sig;
   EnvState* d_state = nullptr;
   EnvPose* d_pose = nullptr;
   EnvState* h_state = nullptr;
@@ -101,6 +117,7 @@ struct tc_context {
   int device = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
+  tc::Signal sig;                    // reads and extractions on `stream`
   uint64_t budget = 0;
   uint64_t used = 0;                 // resident + scratch chunks + plans
   tc::Arena arena;

@@ -75,4 +75,10 @@ inline bool self_timed(KernelId k) {
 // Launch errors surface through hipGetLastError.
 hipError_t launch_kernel(KernelId id, bool fp64, const LaunchArgs& a);
 
+// Copies words x 8 bytes (one block: a few KB) to dst, which may be pinned host
+// memory, then stores seq in the pinned host word *flag: by then everything
+// before it on the stream is done, and a host thread that spins on the word
+// knows so some us before a stream synchronisation returns.
+hipError_t launch_publish(const void* src, void* dst, int words, uint64_t* flag, uint64_t seq, hipStream_t stream);
+
 }  // namespace tc
