@@ -705,7 +705,8 @@ void Runner::launch_tiles(KernelId k, const Tile* tiles, int ntiles, int block, 
   a.parity = parity;
   a.mode = mode;
   a.stream = strm();
-  a.tiles = tiles;
+  // (the CG kernels of a plan of one pad need no list)
+  a.tiles = (k == KernelId::cg_spmv || k == KernelId::cg_update) && P->h_desc.size() == 1 ? nullptr : tiles;
   a.ntiles = ntiles;
   a.block = block;
   a.lpr = P->lpr;
