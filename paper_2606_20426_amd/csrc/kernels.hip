@@ -3780,9 +3780,10 @@ hipError_t launch_typed(KernelId id, const LaunchArgs& a) {
 }
 
 hipError_t launch_publish(const void* src, void* dst, int words, uint64_t* flag, uint64_t seq, hipStream_t stream) {
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(words > 64 ? 1024 : 64), 0, stream, static_cast<const uint64_t*>(src),
-                     static_cast<uint64_t*>(dst), words, flag, seq);
-  return hipGetLastError();
+  // (the launch's own status: the last error may be another call's)
+  void* args[] = {&src, &dst, &words, &flag, &seq};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k_publish), dim3(1), dim3(words > 64 ? 1024 : 64), args, 0,
+                         stream);
 }
 
 hipError_t launch_kernel(KernelId id, bool fp64, const LaunchArgs& a) {

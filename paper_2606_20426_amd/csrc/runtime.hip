@@ -156,7 +156,7 @@ namespace tc {
 
 tc_status Signal::init() {
   if (flag) return TC_OK;
-  TC_HIP(hipHostMalloc(&flag, 64 + PUBLISH_BYTES, hipHostMallocDefault));
+  TC_HIP(hipHostMalloc(&flag, 64 + PUBLISH_BYTES, hipHostMallocCoherent));
   *flag = seq = 0;
   return TC_OK;
 }
@@ -197,7 +197,7 @@ tc_status pool_reserve(tc_context* ctx, SlotPool& p, int cap) {
   if (st) return st;
   TC_HIP(hipMalloc(&p.d_state, sizeof(EnvState) * cap));
   TC_HIP(hipMalloc(&p.d_pose, sizeof(EnvPose) * cap));
-  TC_HIP(hipHostMalloc(&p.h_state, sizeof(EnvState) * cap, hipHostMallocDefault));
+  TC_HIP(hipHostMalloc(&p.h_state, sizeof(EnvState) * cap, hipHostMallocCoherent));   // (kernels store there)
   TC_HIP(hipHostMalloc(&p.h_pose, sizeof(EnvPose) * cap, hipHostMallocDefault));
   p.cap = cap;
   return TC_OK;

@@ -39,6 +39,19 @@ def test_host_reads_return_what_was_written(cells):
     ctx.close()
 
 
+def test_reads_after_another_call_failed():
+    """A read reports its own errors, not the one that an earlier call of the
+    thread left behind."""
+    pad, ind = _pad((4, 3, 2))
+    ctx = tc.Context(0)
+    gp = gpu_pad(ctx, pad, "mixed")
+    assert ctx.lib.hipSetDevice(1 << 20) != 0
+    assert np.array_equal(gp.read("positions"), pad.X)
+    assert ctx.lib.hipGetLastError() != 0      # (and clears it)
+    gp.close()
+    ctx.close()
+
+
 def test_states_beyond_the_limit_are_copied():
     """130 pads' states take more than 32,768 bytes, 2 pads' do not."""
     ctx = tc.Context(0)
