@@ -2139,9 +2139,11 @@ __device__ __forceinline__ double sum8_lane0(double v) {
   return v + dpp<0x55>(v);      // quad_perm [1, 1, 1, 1]
 }
 
+// Row i from its sums: D and gs come in as the sums of the row's records; gs
+// leaves as the gradient, zs as the cold start's z.
 template <typename R>
-__device__ __forceinline__ void asm_diag_row(const EnvDesc& E, int i, double D[3][3], double gs[3], double& rz,
-                                             double& gg, bool warm) {
+__device__ __forceinline__ void asm_diag_row(const EnvDesc& E, int i, double D[3][3], double gs[3], double zs[3],
+                                             bool warm) {
   D[1][0] = D[0][1]; D[2][0] = D[0][2]; D[2][1] = D[1][2];
   const size_t it0 = (size_t)i * E.W;
   const double h2 = E.h * E.h;
@@ -2211,12 +2213,11 @@ __device__ __forceinline__ void asm_diag_row(const EnvDesc& E, int i, double D[3
     const R dp = warm ? d[3 * i + r] : R(0);
     d[3 * i + r] = R(0);
     p1[3 * i + r] = dp;
-    gg += gs[r] * gs[r];
   }
   for (int r = 0; r < 3; ++r) {
     const R zr = Pr[r][0] * (R)rr[0] + Pr[r][1] * (R)rr[1] + Pr[r][2] * (R)rr[2];
     z[3 * i + r] = warm ? R(0) : zr;
-    rz += rr[r] * (double)zr;
+    zs[r] = (double)zr;
   }
 }
 
@@ -2286,22 +2287,32 @@ __global__ void k_asm_diag(const Tile* tiles, int ntiles, const EnvDesc* envs) {
   };
   if (few) take_all(std::true_type());
   else take_all(std::false_type());
-  double rz = 0.0, gg = 0.0;
+  double gs[3] = {0, 0, 0}, zs[3] = {0, 0, 0};
   if (row < E.V) {
     double D[3][3] = {{mine[0], mine[1], mine[2]}, {0, mine[3], mine[4]}, {0, 0, mine[5]}};
-    double gs[3] = {mine[6], mine[7], mine[8]};
-    asm_diag_row<R>(E, row, D, gs, rz, gg, warm);
+    gs[0] = mine[6]; gs[1] = mine[7]; gs[2] = mine[8];
+    asm_diag_row<R>(E, row, D, gs, zs, warm);
   }
-  // the group's rows in order, in its lane 0
-  {
-    double r = 0.0, g = 0.0;
-    for (int k = 0; k < ASM_LPR; ++k) {
-      r += __shfl(rz, k, ASM_LPR);
-      g += __shfl(gg, k, ASM_LPR);
+  // r.z and g.g of the group's rows, one running sum over the components of
+  // rows 0, 1, ..: lane k takes the sum of the rows before its own from lane k -
+  // 1, so it is right from turn k on, and lane 7 ends with all of it.  The order
+  // is part of a step's result: near convergence the line search compares
+  // energies that differ by their rounding, so a last bit here decides how
+  // often Newton iterates and moves stresses in double by 1e-9.
+  double rz = 0.0, gg = 0.0;
+#pragma unroll
+  for (int k = 0; k < ASM_LPR; ++k) {
+    if (k > 0) {
+      rz = dpp<0x111>(rz);      // row_shr:1
+      gg = dpp<0x111>(gg);
     }
-    rz = lane == 0 ? r : 0.0;
-    gg = lane == 0 ? g : 0.0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      rz = fma(-gs[r], zs[r], rz);
+      gg = fma(gs[r], gs[r], gg);
+    }
   }
+  if (lane != ASM_LPR - 1) rz = gg = 0.0;
   rz = block_reduce(rz, OpSum(), sh);
   gg = block_reduce(gg, OpSum(), sh);
   if (threadIdx.x == 0) {
