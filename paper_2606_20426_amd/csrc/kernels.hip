@@ -3694,17 +3694,6 @@ __global__ void k_commit(const Tile* tiles, int ntiles, const EnvDesc* envs) {
 
 // ------------------------------------------------------------ launchers
 
-// One fence for the block, after its waves have waited for their stores: with
-// one a wave (16 write-backs of the XCD's L2), a batch on a second stream ran 1 %
-// slower.
-__global__ void __launch_bounds__(1024) k_publish(const uint64_t* src, uint64_t* dst, int words, uint64_t* flag,
-                                                  uint64_t seq) {
-  for (int i = threadIdx.x; i < words; i += blockDim.x) dst[i] = src[i];
-  __builtin_amdgcn_s_waitcnt(0);        // every wave's stores are acknowledged
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 static inline unsigned grid8(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
 
 // With timing events the dispatch itself carries them (its own start and end
@@ -3788,13 +3777,6 @@ hipError_t launch_typed(KernelId id, const LaunchArgs& a) {
     default: break;
   }
   return err;
-}
-
-hipError_t launch_publish(const void* src, void* dst, int words, uint64_t* flag, uint64_t seq, hipStream_t stream) {
-  // (the launch's own status: the last error may be another call's)
-  void* args[] = {&src, &dst, &words, &flag, &seq};
-  return hipLaunchKernel(reinterpret_cast<const void*>(k_publish), dim3(1), dim3(words > 64 ? 1024 : 64), args, 0,
-                         stream);
 }
 
 hipError_t launch_kernel(KernelId id, bool fp64, const LaunchArgs& a) {

@@ -68,3 +68,33 @@ def test_states_beyond_the_limit_are_copied():
     for p in few + many:
         p.close()
     ctx.close()
+
+
+def test_many_reports():
+    """A report is whole whenever its flag is seen: 400 readings of alternating
+    contents that fill the report, and batches on two streams, each pass of
+    hundreds of state readbacks, that leave the same bits."""
+    ctx = tc.Context(0)
+    pad, ind = _pad((12, 14, 6))
+    gp = gpu_pad(ctx, pad, "mixed")
+    rng = np.random.default_rng(5)
+    xs = [pad.X + 1e-6 * rng.standard_normal(pad.X.shape) for _ in range(2)]
+    for k in range(400):
+        gp.write("positions", xs[k % 2])
+        assert np.array_equal(gp.read("positions"), xs[k % 2]), k
+    gp.close()
+    ctx.set_streams(2)
+    cells = [(4, 3, 2), (11, 7, 5), (13, 14, 4), (20, 16, 5)] * 4
+    made = [_pad(c) for c in cells]
+    pads = [gpu_pad(ctx, p, "mixed", newton_tol=1e-8) for p, _ in made]
+    ref = None
+    for k in range(15):
+        for p in pads:
+            p.reset()
+        tc.step_batch(ctx, pads, [[i] for _, i in made])
+        x = [p.read("positions") for p in pads]
+        ref = ref or x
+        assert all(np.array_equal(a, b) for a, b in zip(ref, x)), k
+    for p in pads:
+        p.close()
+    ctx.close()
