@@ -161,18 +161,22 @@ __device__ double reduce_partials(const double* p, int n, Op op, double init, do
   return block_reduce(v, op, sh);
 }
 
-// Sum of a pad's n >= 1 partials, the same in every thread of every block.
-// Up to 512 each wave sums them itself, in the order of a block of four waves:
-// eight loads a lane, which the constructor issues and sum() waits for, and no
-// barrier; more are shared out over the block, eight loads a thread at a time
+// Sum of a pad's n >= 1 partials, the same in every thread of every block, in
+// the order of a block's strided loop and reduction.  Up to 512 each wave of a
+// block of four, the usual one, sums them itself: eight loads a lane, which the
+// constructor issues and sum() waits for, and no barrier; more, or in a block of
+// another size, are shared out over the block, eight loads a thread at a time
 // (one at a time, the 3,316 of a 1.2M tet pad's products cost its update kernel
 // 9.5 us instead of 7.9, and the 829 of its r.z the product 23.8 instead of 22.4).
 struct PartialSum {
   static constexpr int K = 8;
   double t[K], v;
   int n;
+  bool shared;
   __device__ __forceinline__ PartialSum(gptr<const double> p, int n_) : v(0.0), n(n_) {
-    const int B = blockDim.x, step = n > 64 * K ? B : 64, i = threadIdx.x & (n > 64 * K ? -1 : 63);
+    const int B = blockDim.x;
+    shared = (n > 64 * K) | (B != 256);
+    const int step = shared ? B : 64, i = threadIdx.x & (shared ? -1 : 63);
 #pragma unroll
     for (int k = 0; k < K; ++k) t[k] = p[min(i + step * k, n - 1)];
     if (n > K * B) {
@@ -188,7 +192,7 @@ struct PartialSum {
     }
   }
   __device__ __forceinline__ double sum(double* sh) const {
-    if (n > 64 * K) {
+    if (shared) {
       double w = v;
       if (n <= K * (int)blockDim.x)
 #pragma unroll

@@ -1,5 +1,5 @@
 """Results that do not move from build to build: the first CG iterate and whole
-steps of single pads and of a batch against the bits recorded in
+steps of single pads against the bits recorded in
 golden/step_bits.json.
 
 Every sum of the solver is a fixed tree.  Its order is part of a step's result:
@@ -75,6 +75,22 @@ def episode_bits(cells, prec, warm):
     return out
 
 
+def launch_bits(shape):
+    """Vertex-row and SpMV blocks of other sizes, each with its own order of sums."""
+    pad, ind = _pressed((40, 34, 11))
+    ctx = tc.Context(0)
+    ctx.set_launch(cg_block=shape[0], spmv_block=shape[1])
+    gp = gpu_pad(ctx, pad, "fp64", quasi_static=1, cg_rel_tol=1e-14, cg_forcing=0, max_cg=4)
+    _shaken(gp, pad)
+    out = _digest(*gp.newton_direction([ind]))
+    gp.close()
+    ctx.close()
+    return out
+
+
+SHAPES = [(64, 64), (128, 256), (512, 512), (1024, 128)]
+
+
 def all_bits():
     out = {}
     for prec in ("fp64", "mixed"):
@@ -83,6 +99,8 @@ def all_bits():
         for cells in CELLS[:5]:
             for warm in (0, 1):
                 out[f"episode {cells} {prec} {warm}"] = episode_bits(cells, prec, warm)
+    for shape in SHAPES:
+        out[f"launch {shape}"] = launch_bits(shape)
     return out
 
 
@@ -102,3 +120,8 @@ def test_cg_iterates_keep_their_bits(cells, prec):
 @pytest.mark.parametrize("cells", CELLS[:5])
 def test_steps_keep_their_bits(cells, prec, warm):
     assert episode_bits(cells, prec, warm) == _recorded(f"episode {cells} {prec} {warm}")
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_other_launch_shapes_keep_their_bits(shape):
+    assert launch_bits(shape) == _recorded(f"launch {shape}")
