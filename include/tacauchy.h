@@ -364,10 +364,12 @@ tc_status tc_context_reset_timing(tc_context* ctx);
 
 /* Launch-shape autotuner.  First it times the element and CG kernels on
  * the given pads for each candidate block size (vertex rows and SpMV 128 to
- * 1024, element 64 to 256) and keeps the fastest per kernel; then, by the
+ * 1024, element 64 to 256) and keeps the fastest per kernel (blocks of 256
+ * run the CG of small pads in one block each: where one did, its CG kernels
+ * count together); then, by the
  * wall time of whole probe steps, the number of streams a batch is split
  * over (1 to 4, at least 2 pads each) and the CG iterations between host
- * checks (8, 16, 32), a candidate winning only by more than 2 %.  Every
+ * checks (8, 12, 16, 24), a candidate winning only by more than 2 %.  Every
  * probe starts from the same saved state and leaves the committed pad state
  * unmodified.  chosen (may be NULL) receives 5 values: vertex-row block,
  * element block, SpMV block, CG iterations per host check, streams. */

@@ -1,6 +1,7 @@
 // Runtime behind the C ABI: context, scratch arena, pads, batch plans and the
 // Newton driver that sequences the kernels of kernels.hip.
 #include "runtime.h"
+#include "tune.h"
 
 #include <algorithm>
 #include <chrono>
@@ -2155,7 +2156,7 @@ tc_status tc_autotune(tc_context* ctx, int32_t n, tc_pad* const* pads, const int
     ctx->timing_stride = 1;
     ctx->use_graphs = false;
     // probe: one step per candidate on saved state, restored afterwards
-    auto probe = [&](int vb, int eb, int sb, double* t_spmv, double* t_upd, double* t_el) -> tc_status {
+    auto probe = [&](int vb, int eb, int sb, CgProbe* cg, double* t_el) -> tc_status {
       ctx->cg_block = vb;
       ctx->el_block = eb;
       ctx->spmv_block = sb;
@@ -2179,28 +2180,30 @@ tc_status tc_autotune(tc_context* ctx, int32_t n, tc_pad* const* pads, const int
       }
       if (s && s != TC_E_NOT_CONVERGED && s != TC_E_LINESEARCH) return s;
       resolve_timing(ctx);
-      int64_t cgit = 0;
-      for (auto& x : st) cgit += x.cg_iters;
-      const KernelTimer& ts = ctx->timers[(int)KernelId::cg_spmv];
-      const KernelTimer& tu = ctx->timers[(int)KernelId::cg_update];
+      *cg = CgProbe{vb, ctx->timers[(int)KernelId::cg_spmv].ms, ctx->timers[(int)KernelId::cg_update].ms,
+                    ctx->timers[(int)KernelId::cg_small].ms, 0};
+      for (auto& x : st) cg->its += x.cg_iters;
       const KernelTimer& te = ctx->timers[(int)KernelId::element];
-      *t_spmv = cgit ? ts.ms / (double)cgit : 1e30;
-      *t_upd = cgit ? tu.ms / (double)cgit : 1e30;
       *t_el = te.timed ? te.ms / te.timed : 1e30;
       return TC_OK;
     };
-    int bcg = ctx->cg_block, bel = ctx->el_block, bsp = ctx->spmv_block;
-    double best_u = 1e30, best_s = 1e30, best_e = 1e30;
+    CgChoice cg{ctx->cg_block, ctx->spmv_block};
+    int bel = ctx->el_block;
+    double best_e = 1e30;
+    std::vector<CgProbe> probes;
     for (int b : blk_cands) {
-      double ts, tu, te;
-      tc_status s = probe(b, 128, b, &ts, &tu, &te);
+      CgProbe p;
+      double te;
+      tc_status s = probe(b, 128, b, &p, &te);
       if (s) return s;
-      if (tu < best_u) { best_u = tu; bcg = b; }
-      if (ts < best_s) { best_s = ts; bsp = b; }
+      probes.push_back(p);
     }
+    cg = choose_cg_blocks(probes.data(), (int)probes.size(), cg);
+    const int bcg = cg.vertex_block, bsp = cg.spmv_block;
     for (int eb : el_cands) {
-      double ts, tu, te;
-      tc_status s = probe(bcg, eb, bsp, &ts, &tu, &te);
+      CgProbe p;
+      double te;
+      tc_status s = probe(bcg, eb, bsp, &p, &te);
       if (s) return s;
       if (te < best_e) { best_e = te; bel = eb; }
     }
