@@ -3019,7 +3019,7 @@ __global__ void __launch_bounds__(1024) k_cg_small(const Tile* tiles, const EnvD
     S->cg_stop[0] = S->cg_stop[1] = 1;
     S->cg_done = 1;
     S->cg_iters = it;
-    S->cg_small_its += it + c.warm;
+    S->cg_small_its += it - c.it - 1;   // (this launch's: c.it is the last one before it)
   }
 }
 
