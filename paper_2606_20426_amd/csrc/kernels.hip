@@ -2867,8 +2867,9 @@ template <typename R> constexpr int CG_SMALL_RES = sizeof(R) == 4 ? 4 : 0;
 
 template <typename R>
 __global__ void __launch_bounds__(1024) k_cg_small(const Tile* tiles, const EnvDesc* envs) {
-  constexpr int RES = CG_SMALL_RES<R>, STEPS = 4 * ((CG_SMALL + 255) / 256);
-  __shared__ R sp[3 * CG_SMALL], sq[3 * CG_SMALL];
+  constexpr int ROWS = CG_SMALL_ROWS<R>, RES = CG_SMALL_RES<R>, STEPS = 4 * ((ROWS + 255) / 256);
+  static_assert(ROWS <= 1024 && RES <= 4);
+  __shared__ R sp[3 * ROWS], sq[3 * ROWS];
   __shared__ double s_pq[STEPS / 4][16], s_rz[16];
   // column of each lane's slot in the row steps beyond the resident ones
   __shared__ unsigned short scol[STEPS - RES][1024];

@@ -36,12 +36,12 @@ constexpr int KC = 9;
 constexpr int SPMV_ROWS_PER_GROUP = 4;
 
 // Pads whose CG can run in one block (k_cg_small): rows of at most 16 blocks,
-// and at most this many of them, one per thread of 16 waves.  In double one
-// CU's reads of the matrix cost more than launches beyond 640 rows (both
-// sides measured at the kernel).
-constexpr int CG_SMALL = 1024;
+// and at most this many of them, one per thread of 16 waves; the kernel's arrays
+// are sized by it.  In double the block's reads of the matrix cost more than
+// launches beyond 640 rows (both sides measured at the kernel).
+template <typename R> constexpr int CG_SMALL_ROWS = sizeof(R) == 8 ? 640 : 1024;
 __host__ __device__ constexpr bool cg_small_rows(int V, int W, bool fp64) {
-  return W <= 16 && V <= (fp64 ? 640 : CG_SMALL);
+  return W <= 16 && V <= (fp64 ? CG_SMALL_ROWS<double> : CG_SMALL_ROWS<float>);
 }
 
 // edges per tile of the off-diagonal assembly
