@@ -341,10 +341,11 @@ class Pad:
 
     def read(self, field, device: bool = False):
         """numpy array (host) or torch tensor on the context's device."""
-        layout = self._layouts.get(field)
+        f = FIELDS[field] if isinstance(field, str) else int(field)
+        layout = self._layouts.get(f)
         if layout is None:      # a field's layout never changes
-            layout = self._layouts[field] = self.field_info(field)
-        f, dt, n, c = layout
+            layout = self._layouts[f] = self.field_info(f)
+        _, dt, n, c = layout
         shape = (n, c) if c > 1 else (n,)
         if device:
             import torch
