@@ -864,8 +864,8 @@ __device__ __forceinline__ unsigned group_mask(bool b) {
 //
 // One thread to a primitive walked node by node, each a round trip to memory
 // (121 us an energy pass of 8 pads with 14k primitives, most of which meet
-// nothing); a group takes 16 nodes a round trip, so the walk is as long as the
-// hierarchy is deep.
+// nothing); a group takes 16 nodes a round trip: one for each level of the
+// hierarchy while the front is no wider than that, else one for 16 nodes of it.
 template <typename Leaf>
 __device__ __forceinline__ void bvh_overlap(const DevMesh& M, const double lo[3], const double hi[3], PairWork& W,
                                             Leaf&& leaf) {
@@ -2244,7 +2244,7 @@ __global__ void k_asm_diag(const Tile* tiles, int ntiles, const EnvDesc* envs) {
   // that the records of several rows are on their way together.  Row by row,
   // each waiting for its range and then for each record, with one lane in 8
   // finishing the rows, a launch took 22 us at least (1.9k tets, FP64) and
-  // 72 us on the 60-pad batch; now 14 and 45.
+  // 72 us on the 60-pad batch; now 15 and 45.
   const int row = row0 + lane * groups;
   const int c_beg = row < E.V ? E.dptr[row] : 0;
   const int c_end = row < E.V ? E.dptr[row + 1] : 0;
@@ -2599,9 +2599,9 @@ __device__ __forceinline__ void cg_spmv_rows_body(const Tile tl, const EnvDesc& 
 // tiles, the waves in flight: two rows ahead (76 VGPRs in float) ran the 1.2M
 // tet pad's step 3 % faster than four (110), and a 120k tet one 2.5 % slower.
 // With flat loads, the state tested field by field and reductions through
-// LDS, two steps of the 1.2M tet pad took 95.7 instead of 83.5 ms, of the 120k
-// tet one 34.3 instead of 27.5, and of a 1.9k tet one in FP64 20.0 instead of
-// 15.4, with the same bits.
+// LDS, two steps of the 1.2M tet pad took 95.6 instead of 83.7 ms, of the 120k
+// tet one 33.8 instead of 27.2, and of a 1.9k tet one in FP64 19.4 instead of
+// 15.5 (the performance cases, two inputs each), with the same bits.
 constexpr int SPMV_AHEAD = 2;
 
 template <typename R>
@@ -2855,8 +2855,13 @@ __device__ __forceinline__ void cg_update_tile(const Tile tl, const EnvDesc* env
 // and the choice can look at what else is in the launch.
 //
 // Why: such a pad's launched iteration is two chains of loads and two launch
-// gaps, about 10 us at any size below some 10k tets; here it is the products
-// (one CU reads 64 B/clk from L2) and four barriers.  Two steps of a pad,
+// gaps, about 10 us at any size below some 10k tets; here it is the products and
+// three barriers, in double 7.0 us at 400 rows and 9.9 at 594, in float 3.8 at
+// 400 and 8.6 at 1,001.  The products are not bound by L2, whose 64 B/clk would
+// take 2.5 us at 400 rows in double: 3.0k lines of 128 bytes an iteration are
+// read, the matrix once.  Each of a block's nine loads, 72 bytes from lane to
+// lane, looks its lines up in the L1 again, 22.5k times an iteration (in float
+// 0.6k lines, 5.8k look-ups: half of the row steps are resident).  Two steps of a pad,
 // launched -> here: float, 400 rows 6.0 -> 3.8 ms, 648 rows 7.9 -> 5.2, 1001
 // rows 9.5 -> 7.6; double, 400 rows 9.1 -> 7.0, 648 rows 12.6 -> 10.7, 780
 // rows 11.9 -> 12.3.  Of 40 pads: float, 400 rows 17.9 -> 13.0, 648 rows 21.3

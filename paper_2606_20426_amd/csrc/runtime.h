@@ -69,8 +69,6 @@ struct TimingSlice {
   size_t base = 0, cap = 0, used = 0;
 };
 
-// Device array of per-step states and poses with pinned host mirrors; a pad
-// in a batch occupies one slot.
 // A pinned word (and PUBLISH_BYTES of pinned memory after it) in which a stream
 // reports: publish() copies up to PUBLISH_BYTES there, or to other pinned
 // memory, and returns once everything on the stream is done.  One waiting
@@ -86,6 +84,8 @@ struct Signal {
   tc_status wait(hipStream_t stream) { return publish(nullptr, nullptr, 0, stream); }
 };
 
+// Device array of per-step states and poses with pinned host mirrors; a pad
+// in a batch occupies one slot.
 struct SlotPool {
   int cap = 0;
   Signal sig;
@@ -215,7 +215,7 @@ struct BatchPlan {
   EnvState* h_state = nullptr;      // pinned
   Tile* d_tiles = nullptr;
   size_t dev_bytes = 0;
-  // PAIR: surface triangles and edges (mesh_contact 2)
+  // PAIR: surface triangles, edges and contact vertices (mesh_contact 2)
   // SMALL: one block per pad whose CG can run in one
   enum Cls { VERT, TET, CAND, SURF, ASM, ENERGY, SPMV, PAIR, SMALL, NCLS };
   static int tiles_of(int cls, const EnvDesc& E);

@@ -124,8 +124,9 @@ struct EnvPose {
 constexpr int PAIR_VALUES = 45, PREC = 46;
 
 // Pair kernels: a group of PAIR_LANES lanes to a primitive, its nodes still to
-// be visited (beyond BVH_STACK of them one is taken at a time) and the leaf
-// slots found (emptied from PAIR_LANES on, at most a leaf a lane added at once).
+// be visited (from PAIR_STACK - BVH_STACK = 128 of them on one is taken at a
+// time) and the leaf slots found (emptied from PAIR_LANES on, at most a leaf a
+// lane added at once).
 constexpr int PAIR_LANES = 16, PAIR_BLOCK = 256, PAIR_PRIMS = PAIR_BLOCK / PAIR_LANES;
 constexpr int PAIR_STACK = 128 + BVH_STACK, PAIR_SLOTS = PAIR_LANES * (MESH_LEAF + 1);
 
