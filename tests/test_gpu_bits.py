@@ -1,13 +1,12 @@
-"""Results that do not move from build to build: the first CG iterate and whole
-steps of single pads against the bits recorded in
-golden/step_bits.json.
+"""Results that do not move from version to version: the first CG iterate and whole
+steps of single pads against the bits recorded in golden/step_bits.json.
 
 Every sum of the solver is a fixed tree.  Its order is part of a step's result:
 near convergence the line search compares energies that differ by their
 rounding, so another order of r.z, right to its last bit, changes how often
 Newton iterates and the stresses of a step in double by 1e-9.  The records come
-from a build whose diagonal assembly finished a group's rows one after another in
-a single lane; a build that must change them says so and records anew."""
+from a version whose diagonal assembly finished a group's rows one after another in
+a single lane; a version that must change them says so and records anew."""
 import hashlib
 import json
 import os
